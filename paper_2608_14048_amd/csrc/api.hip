@@ -52,8 +52,8 @@ struct mhd_ctx {
     bool fp32;      // FP32 registers: FP32-bulk MHD form, or FP32 dust (FP64 drag solve)
     // workspace views
     void* reg[3];   // state registers (MHD rotates all three; see reg_view for the layout)
-    void* F;        // MHD: the 9 face fields of the edge EMFs (the path's real type)
-    void* Rc;       // cell-centred E = -v x B (MHD)
+    void* F;        // MHD: the 6 face fields of the edge EMFs (the path's real type)
+    void* Rc;       // cell-centred E = -v x B and the flow codes (MHD)
     FusedGrid fg;   // tiling of the MHD stage kernels
     DustGrid dg;    // tiling of the dust fluid passes
     double* partial;
@@ -211,13 +211,14 @@ Layout layout(const mhd_grid* g, const mhd_physics* p, const mhd_scheme* sc)
     Layout L;
     L.reg = is_mhd ? align256(register_bytes(n, fp32)) : align256(rfield * nv);
     L.nreg = is_mhd ? 3 : 2;
-    // for the FP32 forms the flux area also stages a canonical FP64 state (nv fields);
+    // the flux area holds 6 real fields and, for the FP32 forms, stages a canonical FP64
+    // state (8 fields);
     // the FP64 dust path keeps no arrays besides its two registers
     if (is_mhd)
-        L.F = align256(rfield * 9 > field * 8 ? rfield * 9 : field * 8);
+        L.F = align256(field * 8);
     else
         L.F = fp32 ? align256(field * nv) : 0;
-    L.Rc = is_mhd ? align256(rfield * 3) : 0;
+    L.Rc = is_mhd ? align256(edge_area_bytes(n, fp32)) : 0;
     size_t nb = blocks_for(n);
     const size_t nf = fused_grid(make_geo(g), choose_kz(g)).nblk;
     if (nf > nb) nb = nf;

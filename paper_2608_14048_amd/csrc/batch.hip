@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kFluxThreads) __attribute__((amdgpu_waves_per_eu(Ba
 void k_flux3_batch(const BlockDesc* __restrict__ blk,
                                                              const WorkItem* __restrict__ items, int nitems,
                                                              unsigned long long* ctr, unsigned long long base,
-                                                             MhdParams P, BatchCt a, R* F, R* Rc)
+                                                             MhdParams P, BatchCt a, R* F, R* Rc, unsigned char* S)
 {
     constexpr int TX = SHAPE == 0 ? 64 : (SHAPE == 1 ? 32 : 16);
     using Tile = FluxTile<RECON, RS, IN, R, TX, kFluxThreads / TX>;
@@ -118,7 +118,7 @@ void k_flux3_batch(const BlockDesc* __restrict__ blk,
         const unsigned long long ob = b.off * (unsigned long long)a.reg_bpc;
         const StageArgs<R> s{reg_view<R>(a.in + ob, b.g.n), reg_view<R>(a.base + ob, b.g.n),
                              reg_view<R>(a.out + ob, b.g.n), F + b.off * (unsigned long long)NFACE,
-                             Rc + b.off * 3ULL, StageCoef{a.g0, a.g1, a.beta * a.dt[w.block]}};
+                             Rc + b.off * 3ULL, S + b.off, StageCoef{a.g0, a.g1, a.beta * a.dt[w.block]}};
         Tile::run(b.g, P, s, w.x0, w.y0, w.k0, w.k1, lds);
         __syncthreads();  // the next item reuses the LDS
     }
@@ -130,7 +130,8 @@ template <bool CFL, bool IN, class R, int SHAPE>
 __global__ __launch_bounds__(kCtThreads) void k_ct_batch(const BlockDesc* __restrict__ blk,
                                                         const WorkItem* __restrict__ items, int nitems, int first,
                                                         unsigned long long* ctr, unsigned long long base,
-                                                        MhdParams P, BatchCt a, const R* F, const R* Rc)
+                                                        MhdParams P, BatchCt a, const R* F, const R* Rc,
+                                                        const unsigned char* S)
 {
     constexpr int TX = SHAPE == 0 ? 64 : (SHAPE == 1 ? 32 : 16);
     using Tile = CtTile<CFL, IN, R, TX, kCtThreads / TX>;
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(kCtThreads) void k_ct_batch(const BlockDesc* __rest
         const BlockDesc b = blk[w.block];
         const unsigned long long ob = b.off * (unsigned long long)a.reg_bpc;
         CtArgs<R> c{reg_view<R>(a.in + ob, b.g.n), reg_view<R>(a.base + ob, b.g.n), F + b.off * (unsigned long long)NFACE,
-                    Rc + b.off * 3ULL, reg_view<R>(a.out + ob, b.g.n), nullptr,
+                    Rc + b.off * 3ULL, S + b.off, reg_view<R>(a.out + ob, b.g.n), nullptr,
                     StageCoef{a.g0, a.g1, a.beta * a.dt[w.block]}};
         double vmin = Tile::run(b.g, P, c, w.x0, w.y0, w.k0, w.k1, lds);
         if (CFL) {
@@ -398,7 +399,6 @@ BLayout blayout(int nb, const mhd_grid* grids, const mhd_scheme* s)
 {
     BLayout L;
     const bool fp32 = s->prec == MHD_PREC_FP32_BULK;
-    const size_t rsz = fp32 ? sizeof(float) : sizeof(double);
     unsigned long long o = 0;
     long long cf = 0, cc = 0, maxblk = 1;
     for (int b = 0; b < nb; ++b) {
@@ -419,8 +419,8 @@ BLayout blayout(int nb, const mhd_grid* grids, const mhd_scheme* s)
     L.cap_f = (int)cf;
     L.cap_c = (int)cc;
     L.reg = a256((size_t)o * register_bytes(1, fp32));
-    L.F = a256(std::max((size_t)o * NFACE * rsz, (size_t)o * 8 * sizeof(double)));
-    L.Rc = a256((size_t)o * 3 * rsz);
+    L.F = a256((size_t)o * 8 * sizeof(double));  // 6 face fields, or a canonical FP64 state
+    L.Rc = a256(edge_area_bytes((long long)o, fp32));
     // CFL partials: one per CT item, per workgroup of a block's own reduction, or per
     // workgroup of the reduction over all blocks' cells (a coupled domain)
     L.partial = a256((size_t)std::max({cc, maxblk, (long long)blocks_for((long long)o)}) * sizeof(double));
@@ -517,7 +517,7 @@ void flux_launch(mhd_batch* c, const BatchCt& a)
     const int grid = persistent_grid(c, m);
     hipLaunchKernelGGL((k_flux3_batch<RECON, RS, IN, R, SH>), dim3(grid), dim3(kFluxThreads), 0, c->stream,
                        c->d_blk, c->d_fitems + c->fbeg[SH], m, c->ctr, c->base[0], c->mp, a, (R*)c->F,
-                       (R*)c->Rc);
+                       (R*)c->Rc, flow_area<R>(c->Rc, (long long)c->ncell));
     c->base[0] += (unsigned long long)m + grid;
 }
 
@@ -558,7 +558,7 @@ void ct_launch(mhd_batch* c, const BatchCt& a)
     const int grid = persistent_grid(c, m);
     hipLaunchKernelGGL((k_ct_batch<CFL, IN, R, SH>), dim3(grid), dim3(kCtThreads), 0, c->stream, c->d_blk,
                        c->d_citems + c->cbeg[SH], m, c->cbeg[SH], c->ctr + 1, c->base[1], c->mp, a,
-                       (const R*)c->F, (const R*)c->Rc);
+                       (const R*)c->F, (const R*)c->Rc, flow_area<R>(c->Rc, (long long)c->ncell));
     c->base[1] += (unsigned long long)m + grid;
 }
 

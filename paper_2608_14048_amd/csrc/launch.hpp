@@ -65,10 +65,22 @@ inline size_t register_bytes(long long n, bool fp32)
     return fp32 ? (size_t)n * (sizeof(double) + 7 * sizeof(float)) : (size_t)n * 8 * sizeof(double);
 }
 
+// Bytes per cell of the edge-EMF area `Rc`: the 3 cell-E fields, then one byte of flow
+// codes (the signs of the cell's low-face mass fluxes).
+inline size_t edge_area_bytes(long long n, bool fp32)
+{
+    return (size_t)n * (3 * (fp32 ? sizeof(float) : sizeof(double)) + 1);
+}
+template <class R>
+inline unsigned char* flow_area(void* Rc, long long n)
+{
+    return (unsigned char*)((R*)Rc + 3 * n);
+}
+
 // Fluxes of the stage input `in` and the cell fields of out = g0 in + g1 base + bdt L
-// (out must not alias in or base).  F: the 9 face fields the edge EMFs need (per
-// direction the mass flux and the two face values of E, see FaceField); Rc: 3 fields of
-// the cell E = -v x B (both in the path's real).
+// (out must not alias in or base).  F: the 6 face fields the edge EMFs need (per
+// direction the two face values of E, see FaceField); Rc: 3 fields of the cell E = -v x B
+// (both in the path's real), then the flow codes.
 hipError_t launch_mhd_flux3(const Geo& g, const MhdParams& p, const FusedGrid& fg, bool fp32, int recon,
                             int riemann, void* in, void* base, void* out, void* F, void* Rc, StageCoef coef,
                             hipStream_t s);

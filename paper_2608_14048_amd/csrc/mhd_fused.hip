@@ -3,8 +3,8 @@
 //
 // k_flux3<RECON, RS, IN>  one workgroup = a TXF x TYF tile of xy columns marching a chunk
 //                         of z planes; Riemann solves on every face of the tile, the
-//                         cell fields of the stage output (rho, M, E), and the 9 face
-//                         fields + 3 cell-E fields the edge EMFs need.
+//                         cell fields of the stage output (rho, M, E), and the 6 face
+//                         fields, 3 cell-E fields and flow codes the edge EMFs need.
 // k_ct_update<CFL, IN>    64-lane tiles of 8 rows (one halo row per 8); edge EMFs, the
 //                         face-field update and, in the last stage, the CFL partials.
 //                         The FP64 kernel that also reduces the time step uses 4 rows: it
@@ -139,7 +139,7 @@ static hipError_t flux3_any(const Geo& g, const MhdParams& p, const FusedGrid& f
                             void* in, void* base, void* out, void* F, void* Rc, StageCoef coef, hipStream_t s)
 {
     const StageArgs<R> a{reg_view<R>(in, g.n), reg_view<R>(base, g.n), reg_view<R>(out, g.n), (R*)F, (R*)Rc,
-                         coef};
+                         flow_area<R>(Rc, g.n), coef};
     const bool use_in = coef.g0 != 0.0 || p.gacc[0] != 0.0 || p.gacc[1] != 0.0 || p.gacc[2] != 0.0;
     if (riemann == 1) {
         if (recon == 0) return flux3_in<0, 1, R>(g, p, fg, a, use_in, s);
@@ -165,7 +165,7 @@ static hipError_t ct_update(const Geo& g, const MhdParams& p, const FusedGrid& f
                             double* dt_out, double cfl_scale, hipStream_t s)
 {
     CtArgs<R> a{reg_view<R>(in, g.n), reg_view<R>(base, g.n), (const R*)F, (const R*)Rc,
-                reg_view<R>(out, g.n), partial, coef};
+                flow_area<R>(const_cast<void*>(Rc), g.n), reg_view<R>(out, g.n), partial, coef};
     const bool use_in = coef.g0 != 0.0;
     const unsigned int nb8 = fg.ctx * fg.cty8 * fg.ntz;
     if (dt_out) {

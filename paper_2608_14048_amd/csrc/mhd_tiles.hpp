@@ -10,8 +10,9 @@
 //   face the tile's cells touch; their mass, momentum and energy fluxes meet in LDS and
 //   the cell fields are updated in the same pass (flux divergence of eq. (fv_update),
 //   sources, the two-register combination out = g0 in + g1 base + bdt L).  What the
-//   edge EMFs need leaves the kernel: per face the mass flux and the two face values of
-//   the electric field (E_t1 = F(B_t2), E_t2 = -F(B_t1)), per cell E = -v x B.
+//   edge EMFs need leaves the kernel: per face the two face values of the electric field
+//   (E_t1 = F(B_t2), E_t2 = -F(B_t1)), per cell E = -v x B and one byte with the signs of
+//   the mass fluxes through its low faces.
 //
 // CtTile<CFL, IN, R, TX, TY>: per plane the Gardiner-Stone upwind edge EMFs E_z of the
 //   plane and E_x, E_y of the level above are built in LDS from the face values, the
@@ -111,13 +112,25 @@ struct Raw {
     double E;
 };
 
-template <class R>
-__device__ __forceinline__ Raw<R> load_raw(const Geo& g, const RegView<R>& U, int x, int y, int z)
+// A column of cells: the offset of its cell inside a plane, and whether the cells whose
+// low faces are its high x and y faces lie across the grid's edge.
+struct Column {
+    unsigned int c;
+    bool wx, wy;
+};
+__device__ __forceinline__ Column column(const Geo& g, int x, int y)
 {
-    const unsigned int c = ((unsigned int)z * (unsigned int)g.ny + (unsigned int)y) * (unsigned int)g.nx + x;
-    const unsigned int cx = x + 1 == g.nx ? c - x : c + 1;
-    const unsigned int cy = y + 1 == g.ny ? c - (unsigned int)y * g.nx : c + g.nx;
-    const unsigned int cz = z + 1 == g.nz ? c - (unsigned int)z * g.nx * g.ny : c + (unsigned int)g.nx * g.ny;
+    return Column{(unsigned int)y * (unsigned int)g.nx + (unsigned int)x, x + 1 == g.nx, y + 1 == g.ny};
+}
+
+template <class R>
+__device__ __forceinline__ Raw<R> load_raw(const Geo& g, const RegView<R>& U, const Column& q, int z)
+{
+    const unsigned int plane = (unsigned int)g.nx * (unsigned int)g.ny, zo = (unsigned int)z * plane;
+    const unsigned int c = zo + q.c;
+    const unsigned int cx = c + (q.wx ? 1u - (unsigned int)g.nx : 1u);
+    const unsigned int cy = c + (q.wy ? (unsigned int)g.nx - plane : (unsigned int)g.nx);
+    const unsigned int cz = z + 1 == g.nz ? q.c : c + plane;
     Raw<R> r;
     r.b[0] = ldT(U.b[0], c); r.bh[0] = ldT(U.b[0], cx);
     r.b[1] = ldT(U.b[1], c); r.bh[1] = ldT(U.b[1], cy);
@@ -156,9 +169,18 @@ __device__ __forceinline__ Prim8<R> prims_of(const MhdParams& P, const Raw<R>& r
 
 template <class R>
 __device__ __forceinline__ Prim8<R> load_prims(const Geo& g, const MhdParams& P, const RegView<R>& U,
-                                               int x, int y, int z)
+                                               const Column& q, int z)
 {
-    return prims_of(P, load_raw(g, U, x, y, z));
+    return prims_of(P, load_raw(g, U, q, z));
+}
+
+// A value that is the same in every lane, held in a scalar register (converted from the
+// kernel arguments on the vector unit, it would otherwise keep a vector register through
+// the march).
+__device__ __forceinline__ double uniform(double v) { return v; }
+__device__ __forceinline__ float uniform(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 template <int RS, class R>
@@ -166,9 +188,9 @@ __device__ __forceinline__ void solve(const Prim7<R>& L, const Prim7<R>& Rt, R b
                                       Flux7<R>& f)
 {
     if (RS == 1)
-        riemann_hlld(L, Rt, bn, R(P.gamma), R(P.gm1inv), R(P.hlld_eps), f);
+        riemann_hlld(L, Rt, bn, uniform(R(P.gamma)), uniform(R(P.gm1inv)), uniform(R(P.hlld_eps)), f);
     else
-        riemann_hlle(L, Rt, bn, R(P.gamma), R(P.gm1inv), f);
+        riemann_hlle(L, Rt, bn, uniform(R(P.gamma)), uniform(R(P.gm1inv)), f);
 }
 
 // Reconstruction along z as a pipeline over the planes a column visits: each new plane
@@ -288,14 +310,26 @@ struct StageArgs {
     RegView<R> in;    // stage input register
     RegView<R> base;  // second register; may equal in, never out
     RegView<R> out;   // distinct from in and base
-    R* F;             // 9 face fields: x (mass flux, E_y, E_z), y (mass flux, E_z, E_x),
-                      // z (mass flux, E_x, E_y), each face with the cell on its high side
+    R* F;             // 6 face fields: x (E_y, E_z), y (E_z, E_x), z (E_x, E_y), each face
+                      // with the cell on its high side
     R* Rc;            // 3 cell fields E = -v x B
+    unsigned char* S; // the signs of the cell's three low-face mass fluxes (flow_code)
     StageCoef co;
 };
 
-// Field q of the 9 face fields F (direction-major).
-enum FaceField { FX_MASS = 0, FX_EY, FX_EZ, FY_MASS, FY_EZ, FY_EX, FZ_MASS, FZ_EX, FZ_EY, NFACE };
+// Field q of the 6 face fields F (direction-major).
+enum FaceField { FX_EY = 0, FX_EZ, FY_EZ, FY_EX, FZ_EX, FZ_EY, NFACE };
+
+// The upwind choice of an edge EMF needs only the sign of a face's mass flux: 1 forward,
+// 2 backward, 0 neither (no flux, or not a number).  The codes of a cell's low x, y and z
+// faces share one byte (bits 0, 2, 4): 1 byte per cell written by the flux kernel and read
+// by the CT kernel instead of the three fluxes' 24 (FP64 256^3, HBM-bound CT kernels: 632
+// -> 514 us without and 829 -> 727 us with the time step).
+template <class R>
+__device__ __forceinline__ unsigned int flow_code(R m)
+{
+    return m > R(0) ? 1u : (m < R(0) ? 2u : 0u);
+}
 
 // One tile of the flux/update kernel: TX x TY cells of every plane k0 <= k < k1 (the tile
 // may reach past the grid edge).  Threads: TX * TY, lanes along x first.  Per plane:
@@ -308,8 +342,8 @@ enum FaceField { FX_MASS = 0, FX_EY, FX_EZ, FY_MASS, FY_EZ, FY_EX, FZ_MASS, FZ_E
 //  - the faces' mass, momentum and energy fluxes meet in LDS, and every cell gets the
 //    flux divergence of eq. (fv_update) plus sources and the stage combination, in the
 //    same arithmetic as a separate update pass would use;
-//  - the face values of E and the mass fluxes the edge EMFs need go to F, E = -v x B of
-//    the cell to Rc.
+//  - the face values of E the edge EMFs need go to F, the signs of the mass fluxes to S,
+//    E = -v x B of the cell to Rc.
 template <int RECON, int RS, bool IN, class R, int TX, int TY>
 struct FluxTile {
     static constexpr int SL = Stencil<RECON>::L, SR = Stencil<RECON>::R;
@@ -319,16 +353,35 @@ struct FluxTile {
     static_assert(NR <= NT, "the tile's high faces need TX + TY threads");
     // FP64 PPM: keep the compiler from hoisting the stencil loads of every variable
     // ahead of the reconstructions (it would hold them all in registers at once)
-    static constexpr bool kFence = RECON == 2 && sizeof(R) == 8;
+    static constexpr bool kFence = RECON == 2;
     // FP64 PPM: the z pipeline reloads plane k + 1 instead of carrying it, and the x/y
     // part of a cell's flux divergence is read from LDS when the cell is completed (one
     // more barrier per plane) instead of being carried to the next pass: 24 fewer
     // registers, which lets the kernel run three waves per SIMD
     static constexpr bool kLean = RECON == 2 && sizeof(R) == 8;
+    // PLM: the z pipeline already holds plane k of its column, so the tile's own cells are
+    // staged from it and only the halo is loaded a second time (the planes in flight on an
+    // XCD do not stay in its L2 from one pass to the next: 512 x 512 x 256 FP64 PLM + HLLE,
+    // bandwidth-bound, 5.77 + 6.51 -> 5.40 + 5.67 ms, the donor cell's kept fields aside)
+    static constexpr bool kCarry = RECON == 1;
+    // halo cells of a staged plane: HX columns beside the tile's rows, as many rows above
+    // and below its columns (no corners)
+    static constexpr int HX = SL + SR + 1, NH = HX * (TX + TY);
+    // donor cell: the tile's own cell fields as loaded, kept for the next pass, which
+    // completes them, instead of loading them again (each thread its own cell; in registers
+    // they would cost the FP64 kernel its third wave).  With the flow codes the FP64 HLLD
+    // predictor at 256^3 went from 1354 to 1180 us.
+    struct KeptCells {
+        R u[4][NT];
+        double E[NT];
+    };
+    struct Nothing {};
+    using Kept = std::conditional_t<RECON == 0, KeptCells, Nothing>;
     struct Lds {
         R sw[8][LY][LX];         // primitives of the plane
         R hx[5][TY][TX + 1];     // fluxes through the x faces of the plane's rows
         R hy[5][TY + 1][TX];     // fluxes through the y faces of the plane's columns
+        Kept kept;
     };
 
     // Face states of the seven face-frame variables from a stencil line in LDS: `at(v, s)`
@@ -359,6 +412,7 @@ struct FluxTile {
         // this thread's cell, taken periodically (a lane or row just past the grid edge
         // owns the face at the edge, which is the face at 0)
         const int ic = wrap_any(i, g.nx), jc = wrap_any(j, g.ny);
+        const Column own = column(g, ic, jc);
         // the low faces this thread solves: those of live rows/columns and the grid's
         // high edge when the tile reaches past it
         const bool xneed = i <= g.nx && j < g.ny;
@@ -373,25 +427,28 @@ struct FluxTile {
         // z pipeline of the face-frame variables (rho, v_z, v_x, v_y, p, B_x, B_y); plane
         // k's own values come from the staged plane (a direct load on the last pass)
         Pipe zp[7];
+        R bzk = R(0);  // kCarry: B_z of plane k, beside the pipeline's seven variables
         {
             R pre[7][Pipe::PRIME];
     #pragma unroll
             for (int s = 0; s < Pipe::PRIME; ++s) {
-                const Prim8<R> w = load_prims(g, P, a.in, ic, jc, wrap_any(k0 - Pipe::PRIME + Pipe::AHEAD + s, g.nz));
+                const Prim8<R> w = load_prims(g, P, a.in, own, wrap_any(k0 - Pipe::PRIME + Pipe::AHEAD + s, g.nz));
                 pre[0][s] = w.d; pre[1][s] = w.vz; pre[2][s] = w.vx; pre[3][s] = w.vy;
                 pre[4][s] = w.p; pre[5][s] = w.bx; pre[6][s] = w.by;
+                bzk = w.bz;
             }
     #pragma unroll
             for (int v = 0; v < 7; ++v) zp[v].prime(pre[v]);
         }
         const double bdt = a.co.bdt, g0 = a.co.g0, g1 = a.co.g1;
-        const R bdtr = R(bdt), g0r = R(g0), g1r = R(g1);
-        const R idx = R(g.inv_dx[0]), idy = R(g.inv_dx[1]), idz = R(g.inv_dx[2]);
+        const R bdtr = uniform(R(bdt)), g0r = uniform(R(g0)), g1r = uniform(R(g1));
+        const R idx = uniform(R(g.inv_dx[0])), idy = uniform(R(g.inv_dx[1])), idz = uniform(R(g.inv_dx[2]));
         // carried from one plane to the next: the x/y part of the flux divergence of the
         // cell below (mass and momenta in R, energy in FP64) and the z flux through its
         // low face (mass, M_x, M_y, M_z, E)
         R acc[kLean ? 1 : 4], fzp[5];
         double accE = 0.0;
+        const bool same = a.base.rho == a.in.rho;
     #pragma unroll
         for (int v = 0; v < (kLean ? 1 : 4); ++v) acc[v] = R(0);
     #pragma unroll
@@ -403,64 +460,82 @@ struct FluxTile {
         for (int k = k0; k <= k1; ++k) {
             const bool full = k < k1;
             Prim8<R> wk{}, wz{}, wz1{};
+            Raw<R> rk;
+            // stage the primitives of plane k; the staging waves get issue priority so their
+            // loads go out ahead of the arithmetic of the other workgroups on the CU
+            if (full) __builtin_amdgcn_s_setprio(1);
+            // the column's own cell of plane k (the pipeline's where it holds it), and the
+            // newest plane of the z pipeline (donor cell needs none beyond plane k)
+            if constexpr (kCarry) {
+                wk.d = zp[0].a0; wk.vz = zp[1].a0; wk.vx = zp[2].a0; wk.vy = zp[3].a0;
+                wk.p = zp[4].a0; wk.bx = zp[5].a0; wk.by = zp[6].a0; wk.bz = bzk;
+            } else {
+                rk = load_raw(g, a.in, own, wrap_any(k, g.nz));
+                wk = prims_of(P, rk);
+            }
+            if constexpr (Pipe::AHEAD > 0) wz = load_prims(g, P, a.in, own, wrap_any(k + Pipe::AHEAD, g.nz));
+            if constexpr (kLean) wz1 = load_prims(g, P, a.in, own, wrap_any(k + 1, g.nz));
             if (full) {
-                // stage the primitives of plane k (tile + x/y halos, corners skipped); the
-                // staging waves get issue priority so their loads go out ahead of the
-                // arithmetic of the other workgroups on the CU
-                __builtin_amdgcn_s_setprio(1);
-                for (int t = threadIdx.x; t < LX * LY; t += NT) {
-                    const int r = t / LX, cc = t - r * LX;
-                    const bool xh = cc < SL || cc >= SL + TX, yh = r < SL || r >= SL + TY;
-                    if (xh && yh) continue;
-                    const int gx = wrap_any(x0 + cc - SL, g.nx), gy = wrap_any(y0 + r - SL, g.ny);
-                    const Prim8<R> w = load_prims(g, P, a.in, gx, gy, k);
+                auto put = [&](int r, int cc, const Prim8<R>& w) {
                     sw[0][r][cc] = w.d; sw[1][r][cc] = w.vx; sw[2][r][cc] = w.vy; sw[3][r][cc] = w.vz;
                     sw[4][r][cc] = w.p; sw[5][r][cc] = w.bx; sw[6][r][cc] = w.by; sw[7][r][cc] = w.bz;
+                };
+                put(row + SL, lane + SL, wk);
+                auto halo = [&](int t) {
+                    const bool yh = t < HX * TX;
+                    const int u = t - HX * TX;
+                    const int hr = yh ? t / TX : u % HX, hc = yh ? t % TX : u / HX;
+                    const int e = hr < SL ? hr : hr + (yh ? TY : TX);
+                    const int r = yh ? e : hc + SL, cc = yh ? hc + SL : e;
+                    const int gx = wrap_any(x0 + cc - SL, g.nx), gy = wrap_any(y0 + r - SL, g.ny);
+                    put(r, cc, load_prims(g, P, a.in, column(g, gx, gy), k));
+                };
+                if constexpr (NH <= NT) {
+                    if ((int)threadIdx.x < NH) halo((int)threadIdx.x);
+                } else {
+                    for (int t = threadIdx.x; t < NH; t += NT) halo(t);
                 }
-            } else if constexpr (RECON != 1) {
-                wk = load_prims(g, P, a.in, ic, jc, wrap_any(k, g.nz));
             }
-            // newest plane of the z pipeline (donor cell needs none beyond plane k)
-            if constexpr (Pipe::AHEAD > 0) wz = load_prims(g, P, a.in, ic, jc, wrap_any(k + Pipe::AHEAD, g.nz));
-            if constexpr (kLean) wz1 = load_prims(g, P, a.in, ic, jc, wrap_any(k + 1, g.nz));
             if (full) {
                 __syncthreads();
                 __builtin_amdgcn_s_setprio(0);
             }
 
             const unsigned int kk = (unsigned int)(k < g.nz ? k : k - g.nz);
-            const unsigned int c = kk * plane + (unsigned int)jc * nx + (unsigned int)ic;
+            const unsigned int c = kk * plane + own.c;
             Prim7<R> L, Rt;
             Flux7<R> f;
             // ---- z face k - 1/2 from the pipeline: (rho, vz, vx, vy, p, Bx, By)
             {
-                const int r0 = row + SL, c0 = lane + SL;
                 auto push = [&](Pipe& zpv, R ak, R a1, R a2, R& l, R& r) {
                     if constexpr (kLean)
                         zpv.push(ak, a1, a2, l, r);
                     else
                         zpv.push(ak, a2, l, r);
                 };
-                push(zp[0], full ? sw[0][r0][c0] : wk.d, wz1.d, wz.d, L.d, Rt.d);
-                push(zp[1], full ? sw[3][r0][c0] : wk.vz, wz1.vz, wz.vz, L.vn, Rt.vn);
-                push(zp[2], full ? sw[1][r0][c0] : wk.vx, wz1.vx, wz.vx, L.vt1, Rt.vt1);
-                push(zp[3], full ? sw[2][r0][c0] : wk.vy, wz1.vy, wz.vy, L.vt2, Rt.vt2);
-                push(zp[4], full ? sw[4][r0][c0] : wk.p, wz1.p, wz.p, L.p, Rt.p);
-                push(zp[5], full ? sw[5][r0][c0] : wk.bx, wz1.bx, wz.bx, L.bt1, Rt.bt1);
-                push(zp[6], full ? sw[6][r0][c0] : wk.by, wz1.by, wz.by, L.bt2, Rt.bt2);
+                push(zp[0], wk.d, wz1.d, wz.d, L.d, Rt.d);
+                push(zp[1], wk.vz, wz1.vz, wz.vz, L.vn, Rt.vn);
+                push(zp[2], wk.vx, wz1.vx, wz.vx, L.vt1, Rt.vt1);
+                push(zp[3], wk.vy, wz1.vy, wz.vy, L.vt2, Rt.vt2);
+                push(zp[4], wk.p, wz1.p, wz.p, L.p, Rt.p);
+                push(zp[5], wk.bx, wz1.bx, wz.bx, L.bt1, Rt.bt1);
+                push(zp[6], wk.by, wz1.by, wz.by, L.bt2, Rt.bt2);
             }
+            unsigned int flow = 0;
+            if constexpr (kCarry) bzk = wz.bz;
             if (live) {
                 solve<RS>(L, Rt, ldT(a.in.b[2], c), P, f);
+                flow = flow_code(f.d) << 4;
+                if (full) {
+                    stT(Fo[FZ_EX], c, f.bt2); stT(Fo[FZ_EY], c, -f.bt1);
+                }
                 const R fz[5] = {f.d, f.mt1, f.mt2, f.mn, f.e};
-                // the face's E values and mass flux, stored with the cell above it (the
-                // chunk's first face is stored by the chunk below, as its last)
                 if (k > k0) {
     #pragma clang fp contract(off)
-                    stT(Fo[FZ_MASS], c, f.d); stT(Fo[FZ_EX], c, f.bt2); stT(Fo[FZ_EY], c, -f.bt1);
                     // ---- the cell of plane k - 1: flux divergence (density and momenta
                     // in R, energy in FP64), sources of a constant gas acceleration, the
                     // stage combination
-                    const unsigned int cb = (unsigned int)(k - 1) * plane + (unsigned int)jc * nx + (unsigned int)ic;
+                    const unsigned int cb = (unsigned int)(k - 1) * plane + own.c;
                     R Lc[4];
                     double LE;
                     if constexpr (kLean) {
@@ -484,22 +559,42 @@ struct FluxTile {
                     }
                     R o[4];
                     double oE;
-                    if (IN) {
-                        const R rho_in = ldT(a.in.rho, cb);
-                        const R m_in[3] = {ldT(a.in.m[0], cb), ldT(a.in.m[1], cb), ldT(a.in.m[2], cb)};
-                        Lc[1] += rho_in * R(P.gacc[0]);
-                        Lc[2] += rho_in * R(P.gacc[1]);
-                        Lc[3] += rho_in * R(P.gacc[2]);
-                        LE += ((double)m_in[0] * P.gacc[0] + (double)m_in[1] * P.gacc[1]) + (double)m_in[2] * P.gacc[2];
-                        o[0] = (g0r * rho_in + g1r * ldT(a.base.rho, cb)) + bdtr * Lc[0];
+                    // the cell's fields of the stage input (donor cell: kept from its own
+                    // pass) and of the base register (the input again in a first stage)
+                    R ci[4], cbs[4];
+                    double Ei, Eb;
+                    if constexpr (RECON == 0) {
     #pragma unroll
-                        for (int v = 0; v < 3; ++v) o[1 + v] = (g0r * m_in[v] + g1r * ldT(a.base.m[v], cb)) + bdtr * Lc[1 + v];
-                        oE = (g0 * ldT(a.in.E, cb) + g1 * ldT(a.base.E, cb)) + bdt * LE;
+                        for (int v = 0; v < 4; ++v) ci[v] = lds.kept.u[v][threadIdx.x];
+                        Ei = lds.kept.E[threadIdx.x];
+                    } else if (IN) {
+                        ci[0] = ldT(a.in.rho, cb);
+    #pragma unroll
+                        for (int v = 0; v < 3; ++v) ci[1 + v] = ldT(a.in.m[v], cb);
+                        Ei = ldT(a.in.E, cb);
+                    }
+                    if (RECON == 0 && same) {
+    #pragma unroll
+                        for (int v = 0; v < 4; ++v) cbs[v] = ci[v];
+                        Eb = Ei;
                     } else {
-                        o[0] = g1r * ldT(a.base.rho, cb) + bdtr * Lc[0];
+                        cbs[0] = ldT(a.base.rho, cb);
     #pragma unroll
-                        for (int v = 0; v < 3; ++v) o[1 + v] = g1r * ldT(a.base.m[v], cb) + bdtr * Lc[1 + v];
-                        oE = g1 * ldT(a.base.E, cb) + bdt * LE;
+                        for (int v = 0; v < 3; ++v) cbs[1 + v] = ldT(a.base.m[v], cb);
+                        Eb = ldT(a.base.E, cb);
+                    }
+                    if (IN) {
+                        Lc[1] += ci[0] * uniform(R(P.gacc[0]));
+                        Lc[2] += ci[0] * uniform(R(P.gacc[1]));
+                        Lc[3] += ci[0] * uniform(R(P.gacc[2]));
+                        LE += ((double)ci[1] * P.gacc[0] + (double)ci[2] * P.gacc[1]) + (double)ci[3] * P.gacc[2];
+    #pragma unroll
+                        for (int v = 0; v < 4; ++v) o[v] = (g0r * ci[v] + g1r * cbs[v]) + bdtr * Lc[v];
+                        oE = (g0 * Ei + g1 * Eb) + bdt * LE;
+                    } else {
+    #pragma unroll
+                        for (int v = 0; v < 4; ++v) o[v] = g1r * cbs[v] + bdtr * Lc[v];
+                        oE = g1 * Eb + bdt * LE;
                     }
                     // out never aliases in or base (the host rotates three registers)
                     stT(a.out.rho, cb, o[0]);
@@ -511,6 +606,12 @@ struct FluxTile {
                 for (int v = 0; v < 5; ++v) fzp[v] = fz[v];
             }
             if (!full) break;
+            if constexpr (RECON == 0) {
+                lds.kept.u[0][threadIdx.x] = rk.rho;
+    #pragma unroll
+                for (int v = 0; v < 3; ++v) lds.kept.u[1 + v][threadIdx.x] = rk.m[v];
+                lds.kept.E[threadIdx.x] = rk.E;
+            }
             // lean form: every thread has read the fluxes of plane k - 1 before any
             // thread overwrites them with those of plane k
             if constexpr (kLean) __syncthreads();
@@ -523,7 +624,8 @@ struct FluxTile {
                 lds.hx[0][row][lane] = f.d; lds.hx[1][row][lane] = f.mn; lds.hx[2][row][lane] = f.mt1;
                 lds.hx[3][row][lane] = f.mt2; lds.hx[4][row][lane] = f.e;
                 if (live) {
-                    stT(Fo[FX_MASS], c, f.d); stT(Fo[FX_EY], c, f.bt2); stT(Fo[FX_EZ], c, -f.bt1);
+                    flow |= flow_code(f.d);
+                    stT(Fo[FX_EY], c, f.bt2); stT(Fo[FX_EZ], c, -f.bt1);
                 }
                 if constexpr (kFence) __builtin_amdgcn_sched_barrier(0);
             }
@@ -535,7 +637,9 @@ struct FluxTile {
                 lds.hy[0][row][lane] = f.d; lds.hy[1][row][lane] = f.mt2; lds.hy[2][row][lane] = f.mn;
                 lds.hy[3][row][lane] = f.mt1; lds.hy[4][row][lane] = f.e;
                 if (live) {
-                    stT(Fo[FY_MASS], c, f.d); stT(Fo[FY_EZ], c, f.bt2); stT(Fo[FY_EX], c, -f.bt1);
+                    flow |= flow_code(f.d) << 2;
+                    stT(Fo[FY_EZ], c, f.bt2); stT(Fo[FY_EX], c, -f.bt1);
+                    stT(a.S, c, (unsigned char)flow);
                 }
                 if constexpr (kFence) __builtin_amdgcn_sched_barrier(0);
             }
@@ -621,22 +725,27 @@ struct FluxWaves {
     static constexpr int min = sizeof(R) == 4 ? 4 : (RS == 1 && RECON == 1 ? 2 : 3);
 };
 
+// The candidate on the side the flow comes from (its code at bit b of f), or the mean of
+// both without a flow.
 template <class R>
-__device__ __forceinline__ R gs_upwind(R m, R pos, R neg)
+__device__ __forceinline__ R gs_upwind(unsigned int f, int b, R pos, R neg)
 {
-    return m > R(0) ? pos : (m < R(0) ? neg : R(0.5) * (pos + neg));
+    const R mean = R(0.5) * (pos + neg);
+    const R up = f >> b & 2u ? neg : mean;
+    return f >> b & 1u ? pos : up;
 }
 
 // Gardiner-Stone edge value from the face values X (p-faces) and Y (q-faces), the cell
-// field R at the four cells around the edge and the mass fluxes through the faces.
+// field R at the four cells around the edge and the flow codes of the cells whose low
+// faces meet there: fp0, fpm the p faces' (code at bit p), fq0, fqm the q faces' (at q).
 template <class R>
-__device__ __forceinline__ R gs_edge(R X0, R Xm, R Y0, R Ym, R R00, R Rm0, R R0m, R Rmm, R fp0, R fpm,
-                                     R fq0, R fqm)
+__device__ __forceinline__ R gs_edge(R X0, R Xm, R Y0, R Ym, R R00, R Rm0, R R0m, R Rmm, int p, int q,
+                                     unsigned int fp0, unsigned int fpm, unsigned int fq0, unsigned int fqm)
 {
-    const R dqp = gs_upwind(fp0, Rm0 - Ym, R00 - Y0);
-    const R dqm = gs_upwind(fpm, Ym - Rmm, Y0 - R0m);
-    const R dpp = gs_upwind(fq0, R0m - Xm, R00 - X0);
-    const R dpm = gs_upwind(fqm, Xm - Rmm, X0 - Rm0);
+    const R dqp = gs_upwind(fp0, p, Rm0 - Ym, R00 - Y0);
+    const R dqm = gs_upwind(fpm, p, Ym - Rmm, Y0 - R0m);
+    const R dpp = gs_upwind(fq0, q, R0m - Xm, R00 - X0);
+    const R dpm = gs_upwind(fqm, q, Xm - Rmm, X0 - Rm0);
     return R(0.25) * (((X0 + Xm) + (Y0 + Ym)) - ((dqp - dqm) + (dpp - dpm)));
 }
 
@@ -644,8 +753,9 @@ template <class R>
 struct CtArgs {
     RegView<R> in;       // stage input register
     RegView<R> base;     // second register; may equal in, never out
-    const R* F;          // the 9 face fields of FaceField
+    const R* F;          // the face fields of FaceField
     const R* Rc;         // 3 cell E fields
+    const unsigned char* S;  // flow codes of the low faces
     RegView<R> out;      // distinct from in and base; its cell fields are already updated
     double* partial;     // CFL partial minima, one per workgroup
     StageCoef co;
@@ -686,14 +796,15 @@ struct CtTile {
         auto at = [&](int x, int y, int z) -> unsigned int {
             return (unsigned int)z * plane + (unsigned int)y * nx + (unsigned int)x;
         };
+        auto code = [&](unsigned int c) -> unsigned int { return ldT(a.S, c); };
         // E_x at (x, y-1/2, z-1/2), E_y at (x-1/2, y, z-1/2), E_z at (x-1/2, y-1/2, z)
         auto edge_z = [&](int x, int y, int z) -> R {
             const int xm = wrap_once(x - 1, g.nx), ym = wrap_once(y - 1, g.ny);
             const unsigned int c = at(x, y, z), cx = at(xm, y, z), cy = at(x, ym, z), cxy = at(xm, ym, z);
             // p = x, q = y: X on x-faces, Y on y-faces
             return gs_edge(ldT(Fb[FX_EZ], c), ldT(Fb[FX_EZ], cy), ldT(Fb[FY_EZ], c), ldT(Fb[FY_EZ], cx),
-                           ldT(Rz, c), ldT(Rz, cx), ldT(Rz, cy), ldT(Rz, cxy),
-                           ldT(Fb[FX_MASS], c), ldT(Fb[FX_MASS], cy), ldT(Fb[FY_MASS], c), ldT(Fb[FY_MASS], cx));
+                           ldT(Rz, c), ldT(Rz, cx), ldT(Rz, cy), ldT(Rz, cxy), 0, 2,
+                           code(c), code(cy), code(c), code(cx));
         };
         // Level edges E_x, E_y at z-level zl - 1/2 for the tile (+1 ring on the high side).
         // A thread keeps the same edge positions on every level, so the values of plane
@@ -707,11 +818,13 @@ struct CtTile {
         constexpr bool ZC = !(CFL && sizeof(R) == 8 && TY > 4);
         constexpr int NC = !ZC ? 0 : (sizeof(R) == 4 ? NQ : 1);
         constexpr int NA = NC > 0 ? NC : 1;
-        R cx13[NA], cx7[NA], crx0[NA], crxm[NA], cy5[NA], cy0[NA], cry0[NA], cryx[NA];
+        R cx13[NA], crx0[NA], crxm[NA], cy5[NA], cry0[NA], cryx[NA];
+        unsigned int cf[NA];  // flow code of the edge's own cell
     #pragma unroll
         for (int m = 0; m < NA; ++m) {
-            cx13[m] = cx7[m] = crx0[m] = crxm[m] = R(0);
-            cy5[m] = cy0[m] = cry0[m] = cryx[m] = R(0);
+            cx13[m] = crx0[m] = crxm[m] = R(0);
+            cy5[m] = cry0[m] = cryx[m] = R(0);
+            cf[m] = 0;
         }
         auto fill_level = [&](int slot, int zl, bool first) {
             const int zz = wrap_once(zl, g.nz), zm = wrap_once(zl - 1, g.nz);
@@ -722,40 +835,41 @@ struct CtTile {
                 const int gx = x0 + cc, gy = y0 + r;
                 if (q >= NE || gx > g.nx || gy > g.ny) continue;
                 const int wx = gx == g.nx ? 0 : gx, wy = gy == g.ny ? 0 : gy;
+                const int mc = m < NA ? m : 0;
+                const unsigned int c = at(wx, wy, zz), cz = at(wx, wy, zm);
+                const unsigned int f0 = code(c);
+                const unsigned int fm = first || m >= NC ? code(cz) : cf[mc];  // plane zl - 1
+                if (m < NC) cf[mc] = f0;
                 if (cc < TX && gx < g.nx) {
                     // E_x at (x, y-1/2, z-1/2); p = y, q = z: X on y-faces, Y on z-faces
                     const int ym = wrap_once(wy - 1, g.ny);
-                    const unsigned int c = at(wx, wy, zz), cy = at(wx, ym, zz);
-                    const int mc = m < NA ? m : 0;
-                    R Xm = cx13[mc], R0m = crx0[mc], Rmm = crxm[mc], fpm = cx7[mc];  // plane zl - 1
+                    const unsigned int cy = at(wx, ym, zz);
+                    R Xm = cx13[mc], R0m = crx0[mc], Rmm = crxm[mc];  // plane zl - 1
                     if (first || m >= NC) {
-                        const unsigned int cz = at(wx, wy, zm), cyz = at(wx, ym, zm);
                         Xm = ldT(Fb[FY_EX], cz); R0m = ldT(Rx, cz);
-                        Rmm = ldT(Rx, cyz); fpm = ldT(Fb[FY_MASS], cz);
+                        Rmm = ldT(Rx, at(wx, ym, zm));
                     }
-                    const R X0 = ldT(Fb[FY_EX], c), R00 = ldT(Rx, c), Rm0 = ldT(Rx, cy), fp0 = ldT(Fb[FY_MASS], c);
+                    const R X0 = ldT(Fb[FY_EX], c), R00 = ldT(Rx, c), Rm0 = ldT(Rx, cy);
                     sEx[slot][r][cc] = gs_edge(X0, Xm, ldT(Fb[FZ_EX], c), ldT(Fb[FZ_EX], cy), R00, Rm0, R0m, Rmm,
-                                               fp0, fpm, ldT(Fb[FZ_MASS], c), ldT(Fb[FZ_MASS], cy));
+                                               2, 4, f0, fm, f0, code(cy));
                     if (m < NC) {
-                        cx13[mc] = X0; crx0[mc] = R00; crxm[mc] = Rm0; cx7[mc] = fp0;
+                        cx13[mc] = X0; crx0[mc] = R00; crxm[mc] = Rm0;
                     }
                 }
                 if (r < TY && gy < g.ny) {
                     // E_y at (x-1/2, y, z-1/2); p = z, q = x: X on z-faces, Y on x-faces
                     const int xm = wrap_once(wx - 1, g.nx);
-                    const unsigned int c = at(wx, wy, zz), cx = at(xm, wy, zz);
-                    const int mc = m < NA ? m : 0;
-                    R Ym = cy5[mc], Rm0 = cry0[mc], Rmm = cryx[mc], fqm = cy0[mc];  // plane zl - 1
+                    const unsigned int cx = at(xm, wy, zz);
+                    R Ym = cy5[mc], Rm0 = cry0[mc], Rmm = cryx[mc];  // plane zl - 1
                     if (first || m >= NC) {
-                        const unsigned int cz = at(wx, wy, zm), cxz = at(xm, wy, zm);
                         Ym = ldT(Fb[FX_EY], cz); Rm0 = ldT(Ry, cz);
-                        Rmm = ldT(Ry, cxz); fqm = ldT(Fb[FX_MASS], cz);
+                        Rmm = ldT(Ry, at(xm, wy, zm));
                     }
-                    const R Y0 = ldT(Fb[FX_EY], c), R00 = ldT(Ry, c), R0m = ldT(Ry, cx), fq0 = ldT(Fb[FX_MASS], c);
+                    const R Y0 = ldT(Fb[FX_EY], c), R00 = ldT(Ry, c), R0m = ldT(Ry, cx);
                     sEy[slot][r][cc] = gs_edge(ldT(Fb[FZ_EY], c), ldT(Fb[FZ_EY], cx), Y0, Ym, R00, Rm0, R0m, Rmm,
-                                               ldT(Fb[FZ_MASS], c), ldT(Fb[FZ_MASS], cx), fq0, fqm);
+                                               4, 0, f0, code(cx), f0, fm);
                     if (m < NC) {
-                        cy5[mc] = Y0; cry0[mc] = R00; cryx[mc] = R0m; cy0[mc] = fq0;
+                        cy5[mc] = Y0; cry0[mc] = R00; cryx[mc] = R0m;
                     }
                 }
             }
