@@ -16,11 +16,11 @@
 // operands, FP32 accumulation, v_mfma_f32_16x16x32_bf16 for the 32-channel inputs and
 // v_mfma_f32_16x16x16_bf16 for the first layer's 16 (8 padded).  Activations are
 // stored channel-last ([voxel][channel], channels padded to 16 or 32) so that one
-// lane's K values are one or two 8-byte loads.  A wavefront owns 64 voxels (4 row
-// blocks of 16 along x) x 32 output channels (2 column blocks): 8 accumulators, 27
-// taps x one K step of 8 MFMAs.  The backward data pass is the same kernel on reflected,
-// transposed weights with the ReLU mask of the layer below; the weight gradient is a
-// GEMM over voxels per tap (MFMA with K along voxels) added atomically into FP32.
+// lane's K values are one 8- or 16-byte read.  Persistent workgroups hold the weight
+// fragments of all 27 taps in registers and take 16 x 4 x 8 voxel blocks through LDS
+// (k_conv).  The backward data pass is the same kernel on reflected, transposed weights
+// with the ReLU mask of the layer below; the weight and bias gradients are a GEMM over
+// voxels per tap (MFMA with K along voxels, k_grad) with one partial per workgroup.
 // Master weights and Adam moments are FP32; the BF16 copies are refreshed after each
 // update.
 //
@@ -47,24 +47,13 @@ constexpr int kCout[kLayers] = {32, 32, 32, 18};
 constexpr int kCinPad[kLayers] = {16, 32, 32, 32};
 constexpr int kNPad = 32;        // padded output width of every layer
 constexpr int kThreads = 256;    // 4 wavefronts
-constexpr int kVoxPerWave = 64;
 
 typedef unsigned short bf16_t;
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef short s8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
-
-// One 16 x 16 output block times a K chunk: 32 channels per instruction
-// (v_mfma_f32_16x16x32_bf16: lane l holds A row l % 16 and B column l % 16 at K
-// 8 (l / 16) + 0..7; checked on the device) where the layer input is a multiple of 32
-// channels wide, else 16 (v_mfma_f32_16x16x16_bf16, K 4 (l / 16) + 0..3).  Both
-// convolution forms step through K the same way, so they give the same bits.
-__device__ __forceinline__ f4 mfma_k32(s4 alo, s4 ahi, s8 b, f4 c)
-{
-    const s8 a = {alo[0], alo[1], alo[2], alo[3], ahi[0], ahi[1], ahi[2], ahi[3]};
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
-}
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 
 constexpr size_t layer_w(int l) { return (size_t)27 * kCin[l] * kCout[l]; }
 constexpr size_t layer_params(int l) { return layer_w(l) + kCout[l]; }
@@ -83,9 +72,22 @@ __device__ __forceinline__ bf16_t f2bf(float x)
     u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
     return (bf16_t)(u >> 16);
 }
+// two at once, the first in the low half (the hardware conversion: nearest even too)
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi)
+{
+    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf2{(__bf16)lo, (__bf16)hi});
+}
 __device__ __forceinline__ float bf2f(bf16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 __device__ __forceinline__ int wrap1(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
+
+// i taken periodically into [0, n) from any distance
+__device__ __forceinline__ int wrapn(int i, int n)
+{
+    const int r = i % n;
+    return r < 0 ? r + n : r;
+}
 
 // voxel index of (x, y, z) displaced by tap t
 __device__ __forceinline__ unsigned int tap_voxel(const Geo& g, int x, int y, int z, int t)
@@ -135,303 +137,369 @@ __global__ __launch_bounds__(kThreads) void k_cnn_input(Geo g, double gamma, con
 // Y[v][nn] = sum_t sum_k X[v + off(t)][k] B[t][nn][k] (+ bias), 32 outputs.
 // MODE 0: + bias, ReLU, store BF16 [n][32].  MODE 1: + bias, store FP32 planar O[nn][v]
 // for nn < nstore.  MODE 2: times (M[v][nn] > 0), store BF16 [n][32].
+//
+// Persistent workgroups of eight waves, two per SIMD, so that a wave may hold 256
+// registers: its 16 output channels' weight fragments of all 27 taps stay in them (108 at
+// 32 input channels), read from memory once per wave instead of once per block.  A block
+// is 16 x 4 x 8 voxels, its input with a one-voxel halo (18 x 6 x 10 voxels) is staged in
+// LDS while the loads of the next block's are in flight, and wave w computes channels
+// 16 (w % 2) .. of the 4 rows of planes 2 (w / 2) and the one above.  An input row's
+// fragment is read once per dx and serves every (dy, dz) that reaches it: 72 LDS reads for
+// 216 matrix instructions (one read per instruction when each tap read its own).  Every
+// output still adds its taps in the order t = 0 .. 26.  Rows past the grid's edge are
+// computed from any rows and not stored.  64^3, 32 -> 32 channels: 30.8 -> 22.2 us forward,
+// 41.5 -> 24.5 us with the ReLU mask, against a block per workgroup of four waves that
+// fetched each tap's weights from L2 (of 22 us about 7 are the launch and the staging of
+// two blocks, 4 the weights, 10 the matrix instructions and their LDS reads).  The weight
+// fragments are the first operand where the output is channel-last, so that a lane ends
+// up with four channels of a voxel and stores 8 bytes.
+constexpr int kTileY = 4, kTileZ = 8;
+constexpr int kConvThreads = 512, kConvWaves = kConvThreads / 64;
+constexpr int kConvGroups = 256;  // persistent workgroups at most: one per CU
+
+template <int CINP>
+struct ConvFrag;
+template <>
+struct ConvFrag<32> {
+    typedef s8 T;
+    // D rows are the first operand's, columns the second's
+    __device__ static f4 mma(T a, T b, f4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+    }
+};
+template <>
+struct ConvFrag<16> {
+    typedef s4 T;
+    __device__ static f4 mma(T a, T b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0); }
+};
+
 template <int CINP, int MODE>
-__global__ __launch_bounds__(kThreads) void k_conv(Geo g, const bf16_t* __restrict__ X, const bf16_t* __restrict__ B,
-                                                   const float* __restrict__ bias, const bf16_t* __restrict__ M,
-                                                   bf16_t* __restrict__ Y, float* __restrict__ O, int nstore)
+__global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_conv(
+    Geo g, const bf16_t* __restrict__ X, const bf16_t* __restrict__ B, const float* __restrict__ bias,
+    const bf16_t* __restrict__ M, bf16_t* __restrict__ Y, float* __restrict__ O, int nstore, unsigned int nty,
+    unsigned int nblk)
 {
-    const int lane = threadIdx.x & 63;
-    const unsigned int v0 = (blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kVoxPerWave;
-    const unsigned int n = (unsigned int)g.n;
-    if (v0 >= n) return;  // the whole wavefront (n is a multiple of 16, blocks of 16 stay in one row)
-    const int lr = lane & 15, lk = (lane >> 4) * 4;
-    int bx[4], by[4], bz[4];
-    bool live[4];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-        const unsigned int vb = v0 + rb * 16;
-        live[rb] = vb < n;
-        const unsigned int vv = live[rb] ? vb : v0;
-        bx[rb] = (int)(vv % (unsigned int)g.nx) + lr;
-        by[rb] = (int)((vv / (unsigned int)g.nx) % (unsigned int)g.ny);
-        bz[rb] = (int)(vv / ((unsigned int)g.nx * (unsigned int)g.ny));
-    }
-    f4 acc[4][2];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int t = 0; t < 27; ++t) {
-        unsigned int vs[4];
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb) vs[rb] = tap_voxel(g, bx[rb], by[rb], bz[rb], t);
-        if constexpr (CINP % 32 == 0) {
-            const int lk8 = (lane >> 4) * 8;
-#pragma unroll
-            for (int kc = 0; kc < CINP / 32; ++kc) {
-                s8 bf[2];
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
-                    bf[cb] = *reinterpret_cast<const s8*>(B + ((size_t)(t * kNPad + cb * 16 + lr) * CINP + kc * 32 + lk8));
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    const bf16_t* xa = X + ((size_t)vs[rb] * CINP + kc * 32 + lk8);
-                    const s4 alo = *reinterpret_cast<const s4*>(xa), ahi = *reinterpret_cast<const s4*>(xa + 4);
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = mfma_k32(alo, ahi, bf[cb], acc[rb][cb]);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int kc = 0; kc < CINP / 16; ++kc) {
-                s4 bf[2];
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
-                    bf[cb] = *reinterpret_cast<const s4*>(B + ((size_t)(t * kNPad + cb * 16 + lr) * CINP + kc * 16 + lk));
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    const s4 af = *reinterpret_cast<const s4*>(X + ((size_t)vs[rb] * CINP + kc * 16 + lk));
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
-                        acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, bf[cb], acc[rb][cb], 0, 0, 0);
-                }
-            }
-        }
-    }
-    // accumulator element i of lane l: row (voxel) 4*(l/16) + i, column (channel) l % 16
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-        if (!live[rb]) continue;
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            const int nn = cb * 16 + lr;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned int v = v0 + rb * 16 + lk + i;
-                float val = acc[rb][cb][i];
-                if (MODE == 0) {
-                    val = fmaxf(val + bias[nn], 0.f);
-                    Y[(size_t)v * kNPad + nn] = f2bf(val);
-                } else if (MODE == 1) {
-                    if (nn < nstore) O[(size_t)nn * n + v] = val + bias[nn];
-                } else {
-                    if (!(bf2f(M[(size_t)v * kNPad + nn]) > 0.f)) val = 0.f;
-                    Y[(size_t)v * kNPad + nn] = f2bf(val);
-                }
-            }
-        }
-    }
-}
+    using Frag = ConvFrag<CINP>;
+    using T = typename Frag::T;
+    constexpr int KL = CINP / 4;                     // K values of a lane
+    constexpr int CH = CINP / 8;                     // 16-byte chunks of a voxel
+    constexpr int HY = kTileY + 2, HZ = kTileZ + 2, ROWS = HY * HZ;
+    constexpr int NR = (ROWS + kConvWaves - 1) / kConvWaves;
+    // a wave stages rows w, w + 8, ..: one load for a row's first 16 voxels (all 18 where
+    // they fit the 64 lanes), and one for the last two voxels of eight rows
+    constexpr int MV = CH == 2 ? 18 : 16, NTAIL = CH == 2 ? 0 : (NR + 7) / 8;
+    // chunk c of a voxel in column x sits at c ^ swz(x): sixteen consecutive voxels of one
+    // chunk then spread over all banks
+    __shared__ __align__(16) bf16_t sA[18 * ROWS * CINP];
+    auto swz = [](int x) { return CINP == 32 ? (x >> 2) & 3 : (x >> 3) & 1; };
+    const int lane = (int)threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int zp = 2 * (w >> 1), cb = w & 1;  // this wave's planes (zp, zp + 1) and channel half
+    const int lr = lane & 15, lg = lane >> 4;
+    const unsigned int ntx = (unsigned int)g.nx / 16u, n = (unsigned int)g.n;
 
-// The same convolution with its input staged in LDS: one workgroup computes a
-// 16 x 4 x 4TZ block of voxels (wave w the 4 rows of planes z0 + TZ w ..), and the
-// block's input with a one-voxel halo, 18 x 6 x (4TZ + 2) voxels of CINP channels, is
-// read from memory once into LDS instead of once per tap; every tap's A fragments then
-// come from LDS.  The accumulation order (taps, then K chunks) is that of k_conv, so
-// the results are bitwise the same.  Needs ny a multiple of 4 and nz one of 4TZ (nx is
-// one of 16).
-constexpr int kTileY = 4;
-
-// TZ: planes per wavefront (the block is 16 x 4 x 4 TZ voxels)
-template <int CINP, int MODE, int TZ>
-__global__ __launch_bounds__(kThreads) void k_conv_lds(Geo g, const bf16_t* __restrict__ X,
-                                                       const bf16_t* __restrict__ B,
-                                                       const float* __restrict__ bias,
-                                                       const bf16_t* __restrict__ M, bf16_t* __restrict__ Y,
-                                                       float* __restrict__ O, int nstore)
-{
-    constexpr int CSTR = CINP + 4;  // channels per staged voxel, padded (8-byte aligned rows)
-    constexpr int kTileZ = 4 * TZ, kHalo = 18 * (kTileY + 2) * (kTileZ + 2);
-    constexpr int NRB = 4 * TZ;     // 16-voxel row blocks per wavefront
-    __shared__ __align__(16) bf16_t sA[kTileZ + 2][kTileY + 2][18][CSTR];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const unsigned int ntx = (unsigned int)g.nx / 16u, nty = (unsigned int)g.ny / kTileY;
-    const unsigned int b = blockIdx.x;
-    const int x0 = (int)(b % ntx) * 16;
-    const int y0 = (int)((b / ntx) % nty) * kTileY;
-    const int z0 = (int)(b / (ntx * nty)) * kTileZ;
-    const unsigned int n = (unsigned int)g.n;
-
-    // stage the input block with its halo (periodic), 16 bytes per load (two 8-byte LDS
-    // writes: the padded LDS rows are 8-byte aligned only)
-    constexpr int CH = CINP / 8;
-    for (int q = threadIdx.x; q < kHalo * CH; q += kThreads) {
-        const int vq = q / CH, part = q - vq * CH;
-        const int lx = vq % 18, ly = (vq / 18) % (kTileY + 2), lz = vq / (18 * (kTileY + 2));
-        const unsigned int gv = ((unsigned int)wrap1(z0 + lz - 1, g.nz) * (unsigned int)g.ny +
-                                 (unsigned int)wrap1(y0 + ly - 1, g.ny)) * (unsigned int)g.nx +
-                                (unsigned int)wrap1(x0 + lx - 1, g.nx);
-        const uint4 v = *reinterpret_cast<const uint4*>(X + (size_t)gv * CINP + part * 8);
-        *reinterpret_cast<uint2*>(&sA[lz][ly][lx][part * 8]) = uint2{v.x, v.y};
-        *reinterpret_cast<uint2*>(&sA[lz][ly][lx][part * 8 + 4]) = uint2{v.z, v.w};
-    }
-    __syncthreads();
-
-    const int lr = lane & 15, lk = (lane >> 4) * 4;
-    // row block rb of wave w: row y0 + rb % 4 of plane z0 + TZ w + rb / 4
-    f4 acc[NRB][2];
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = f4{0.f, 0.f, 0.f, 0.f};
-    // The weight fragments of tap t + 1 are loaded while tap t multiplies: they come from
-    // L2 (a layer's weights do not fit L1), and waiting for them at every tap left the
-    // matrix cores idle most of the time.
-    if constexpr (CINP % 32 == 0) {
-        const int lk8 = (lane >> 4) * 8;
-        auto load_b = [&](int t, s8 (&bf)[CINP / 32][2]) {
-#pragma unroll
-            for (int kc = 0; kc < CINP / 32; ++kc)
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
-                    bf[kc][cb] = *reinterpret_cast<const s8*>(
-                        B + ((size_t)(t * kNPad + cb * 16 + lr) * CINP + kc * 32 + lk8));
+    const int mvox = lane / CH, mpos = lane % CH;          // this lane's voxel and chunk of a row
+    const int tvox = 16 + (lane >> 2 & 1), tpos = lane & 3;  // and of a row's tail
+    u4 v[NR], tail[NTAIL > 0 ? NTAIL : 1];
+    auto fetch = [&](unsigned int blk) {
+        const int x0 = (int)(blk % ntx) * 16, y0 = (int)((blk / ntx) % nty) * kTileY;
+        const int z0 = (int)(blk / (ntx * nty)) * kTileZ;
+        // first voxel of halo row r of the block (periodic)
+        auto line = [&](int r) {
+            int y = y0 + r % HY - 1, z = z0 + r / HY - 1;
+            if (y < 0) y += g.ny;
+            if (z < 0) z += g.nz;
+            while (y >= g.ny) y -= g.ny;
+            while (z >= g.nz) z -= g.nz;
+            return ((unsigned int)z * (unsigned int)g.ny + (unsigned int)y) * (unsigned int)g.nx;
         };
-        s8 bcur[CINP / 32][2], bnxt[CINP / 32][2];
-        load_b(0, bcur);
-        for (int t = 0; t < 27; ++t) {
-            const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-            load_b(t < 26 ? t + 1 : t, bnxt);
+        const unsigned int mo = (unsigned int)wrap1(x0 + mvox - 1, g.nx) * CINP + (mpos ^ swz(mvox)) * 8;
 #pragma unroll
-            for (int kc = 0; kc < CINP / 32; ++kc) {
-#pragma unroll
-                for (int rb = 0; rb < NRB; ++rb) {
-                    // two 8-byte reads: the padded LDS rows are 8-byte aligned only
-                    const bf16_t* xa = &sA[TZ * w + rb / 4 + dz + 1][rb % 4 + dy + 1][lr + dx + 1][kc * 32 + lk8];
-                    const s4 alo = *reinterpret_cast<const s4*>(xa), ahi = *reinterpret_cast<const s4*>(xa + 4);
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = mfma_k32(alo, ahi, bcur[kc][cb], acc[rb][cb]);
-                }
-            }
-#pragma unroll
-            for (int kc = 0; kc < CINP / 32; ++kc)
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb) bcur[kc][cb] = bnxt[kc][cb];
+        for (int m = 0; m < NR; ++m) {
+            const int r = w + kConvWaves * m;
+            const bf16_t* p = X + (size_t)line(r < ROWS ? r : 0) * CINP;  // (row 0 again past the last)
+            if (mvox < MV) v[m] = *reinterpret_cast<const u4*>(reinterpret_cast<const char*>(p) + mo * 2u);
         }
-    } else {
-        for (int t = 0; t < 27; ++t) {
-            const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
 #pragma unroll
-            for (int kc = 0; kc < CINP / 16; ++kc) {
-                s4 bf[2];
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
-                    bf[cb] = *reinterpret_cast<const s4*>(B + ((size_t)(t * kNPad + cb * 16 + lr) * CINP + kc * 16 + lk));
-#pragma unroll
-                for (int rb = 0; rb < NRB; ++rb) {
-                    const s4 af = *reinterpret_cast<const s4*>(
-                        &sA[TZ * w + rb / 4 + dz + 1][rb % 4 + dy + 1][lr + dx + 1][kc * 16 + lk]);
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
-                        acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, bf[cb], acc[rb][cb], 0, 0, 0);
-                }
+        for (int m = 0; m < NTAIL; ++m) {
+            const int rr = m * 8 + (lane >> 3);
+            if (w + kConvWaves * rr < ROWS) {
+                const unsigned int gv = line(w + kConvWaves * rr) + (unsigned int)wrap1(x0 + tvox - 1, g.nx);
+                tail[m] = *reinterpret_cast<const u4*>(X + (size_t)gv * CINP + (tpos ^ swz(tvox)) * 8);
             }
         }
+    };
+    fetch(blockIdx.x);  // the grid has at most nblk workgroups
+    T wt[27];
+#pragma unroll
+    for (int t = 0; t < 27; ++t)  // (a scalar base and one lane offset: no address registers)
+        wt[t] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(B + (t * kNPad + cb * 16) * CINP) +
+                                            (unsigned int)(lr * CINP + lg * KL) * 2u);
+
+    // where this lane reads the fragments of its first halo row (the others lie a constant
+    // number of bytes further on)
+    const bf16_t* a0[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) {
+        const int x = lr + dx, chunk = CINP == 32 ? lg : lg >> 1, part = CINP == 32 ? 0 : (lg & 1) * 4;
+        a0[dx] = sA + (zp * HY * 18 + x) * CINP + (chunk ^ swz(x)) * 8 + part;
     }
-    // accumulator element i of lane l: row (voxel) 4*(l/16) + i, column (channel) l % 16
+
+    for (unsigned int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+        __syncthreads();  // the block before is read
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-        const unsigned int vrow = ((unsigned int)(z0 + TZ * w + rb / 4) * (unsigned int)g.ny +
-                                   (unsigned int)(y0 + rb % 4)) * (unsigned int)g.nx + (unsigned int)x0;
+        for (int m = 0; m < NR; ++m)
+            if (mvox < MV && w + kConvWaves * m < ROWS)
+                *reinterpret_cast<u4*>(sA + (size_t)((w + kConvWaves * m) * 18 + mvox) * CINP + mpos * 8) = v[m];
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            const int nn = cb * 16 + lr;
+        for (int m = 0; m < NTAIL; ++m) {
+            const int rr = m * 8 + (lane >> 3);
+            if (w + kConvWaves * rr < ROWS)
+                *reinterpret_cast<u4*>(sA + (size_t)((w + kConvWaves * rr) * 18 + tvox) * CINP + tpos * 8) = tail[m];
+        }
+        __syncthreads();
+        if (blk + gridDim.x < nblk) fetch(blk + gridDim.x);
+
+        // acc[rb]: row rb % 4 of plane zp + rb / 4
+        f4 acc[8];
+#pragma unroll
+        for (int rb = 0; rb < 8; ++rb) acc[rb] = f4{0.f, 0.f, 0.f, 0.f};
+        // the fragments of input row r (row r % HY of plane zp + r / HY of the halo block),
+        // one per dx; those of row r + 1 are read while row r multiplies
+        auto row = [&](int r, int dx) { return *reinterpret_cast<const T*>(a0[dx] + r * (18 * CINP)); };
+        T cur[3], nxt[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) cur[dx] = nxt[dx] = row(0, dx);
+#pragma unroll
+        for (int r = 0; r < 4 * HY; ++r) {
+            if (r + 1 < 4 * HY) {
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) nxt[dx] = row(r + 1, dx);
+            }
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                for (int z = 0; z < 2; ++z)
+#pragma unroll
+                    for (int y = 0; y < kTileY; ++y) {
+                        const int dz = r / HY - z, dy = r % HY - y;
+                        if (dz < 0 || dz > 2 || dy < 0 || dy > 2) continue;
+                        const int t = dz * 9 + dy * 3 + dx;
+                        f4& d = acc[z * 4 + y];
+                        d = MODE == 1 ? Frag::mma(cur[dx], wt[t], d) : Frag::mma(wt[t], cur[dx], d);
+                    }
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) cur[dx] = nxt[dx];
+            __builtin_amdgcn_sched_barrier(0);  // (all rows' reads at once would not fit the registers)
+        }
+        // MODE 1: element i of lane l is voxel 4 (l / 16) + i of the row, channel l % 16;
+        // else voxel l % 16, channel 4 (l / 16) + i: four voxels or four channels per store
+        const int x0 = (int)(blk % ntx) * 16, y0 = (int)((blk / ntx) % nty) * kTileY;
+        const int z0 = (int)(blk / (ntx * nty)) * kTileZ + zp;
+#pragma unroll
+        for (int rb = 0; rb < 8; ++rb) {
+            const int y = y0 + rb % 4, z = z0 + rb / 4;
+            if (y >= g.ny || z >= g.nz) continue;
+            const unsigned int vrow = ((unsigned int)z * (unsigned int)g.ny + (unsigned int)y) * (unsigned int)g.nx +
+                                      (unsigned int)x0;
+            const f4 a = acc[rb];
             if constexpr (MODE == 1) {
-                // the four voxels of a lane are consecutive: one 16-byte store
+                const int nn = cb * 16 + lr;
                 if (nn < nstore) {
                     const float b = bias[nn];
-                    const float4 o4 = {acc[rb][cb][0] + b, acc[rb][cb][1] + b, acc[rb][cb][2] + b,
-                                       acc[rb][cb][3] + b};
-                    *reinterpret_cast<float4*>(O + (size_t)nn * n + vrow + lk) = o4;
+                    *reinterpret_cast<float4*>(O + (size_t)nn * n + vrow + lg * 4) =
+                        float4{a[0] + b, a[1] + b, a[2] + b, a[3] + b};
                 }
             } else {
+                const size_t at = (size_t)(vrow + lr) * kNPad + cb * 16 + lg * 4;
+                float o[4];
+                if constexpr (MODE == 0) {
+                    const float4 b = *reinterpret_cast<const float4*>(bias + cb * 16 + lg * 4);
+                    o[0] = fmaxf(a[0] + b.x, 0.f); o[1] = fmaxf(a[1] + b.y, 0.f);
+                    o[2] = fmaxf(a[2] + b.z, 0.f); o[3] = fmaxf(a[3] + b.w, 0.f);
+                } else {
+                    const uint2 mk = *reinterpret_cast<const uint2*>(M + at);
+                    o[0] = __uint_as_float(mk.x << 16) > 0.f ? a[0] : 0.f;
+                    o[1] = __uint_as_float(mk.x & 0xffff0000u) > 0.f ? a[1] : 0.f;
+                    o[2] = __uint_as_float(mk.y << 16) > 0.f ? a[2] : 0.f;
+                    o[3] = __uint_as_float(mk.y & 0xffff0000u) > 0.f ? a[3] : 0.f;
+                }
+                *reinterpret_cast<uint2*>(Y + at) = uint2{f2bf2(o[0], o[1]), f2bf2(o[2], o[3])};
+            }
+        }
+    }
+}
+
+// Weight and bias gradients of one layer, dW[t][k][nn] = sum_v X[v + off(t)][k] D[v][nn]
+// and db[nn] = sum_v D[v][nn], one partial per workgroup (k_grad_sum adds them up).
+//
+// A GEMM per tap with K along the voxels, v_mfma_f32_32x32x16_bf16 (lane l holds A row and
+// B column l % 32 at K 8 (l / 32) + 0..7).  The operands are channel-last in memory and a
+// lane needs eight voxels of one channel, so a block of 16 x 4 x 4 voxels (X with its
+// one-voxel halo) is transposed into LDS once, four voxels per write, and all 27 taps
+// read it there: wave w owns the three taps dx = -1, 0, 1 of one (dy, dz), which are three
+// windows of the same ten voxels (dx = 0 is the odd one, shifted out of its neighbours).
+// Nine waves, 48 accumulator registers each, kept over all the blocks a workgroup takes.
+// 64^3, 32 -> 32 channels: gathering two bytes at a time for every tap with one atomic add
+// per gradient and chunk took 239 us and the bias gradient's own pass 32; this takes 29,
+// and 6 to add the partials up.  Two workgroups per CU (96 registers, spilling, twice the
+// partials) took 38 + 9.
+constexpr int kGradWaves = 9, kGradThreads = 64 * kGradWaves;
+constexpr int kGradGroups = 256;  // workgroups at most (one per CU), each with its own partial
+constexpr int kXRow = 10;                      // dwords of a staged X row: voxels x0 - 1 .. x0 + 16, padded
+constexpr int kXStr = 36 * kXRow + 2;          // dwords of a channel (36 rows), bank-spread
+constexpr int kDStr = 16 * 8 + 4;              // dwords of a D channel (16 rows of 16 voxels)
+
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+// Eight channels of four voxels (v[j]: voxel j) transposed: q[c] = channel c's four voxels.
+__device__ __forceinline__ void transpose_8x4(const u4 v[4], uint2 q[8])
+{
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const unsigned int v = vrow + lk + i;
-                    float val = acc[rb][cb][i];
-                    if (MODE == 0) {
-                        val = fmaxf(val + bias[nn], 0.f);
-                    } else {
-                        if (!(bf2f(M[(size_t)v * kNPad + nn]) > 0.f)) val = 0.f;
-                    }
-                    Y[(size_t)v * kNPad + nn] = f2bf(val);
+    for (int c = 0; c < 4; ++c) {
+        const unsigned int a = v[0][c], b = v[1][c], d = v[2][c], e = v[3][c];
+        q[2 * c] = uint2{(a & 0xffffu) | b << 16, (d & 0xffffu) | e << 16};
+        q[2 * c + 1] = uint2{a >> 16 | (b & 0xffff0000u), d >> 16 | (e & 0xffff0000u)};
+    }
+}
+
+template <int CINP>
+__global__ __launch_bounds__(kGradThreads) void k_grad(Geo g, const bf16_t* __restrict__ X,
+                                                       const bf16_t* __restrict__ D, float* __restrict__ part, int cin,
+                                                       int cout, unsigned int nty, unsigned int nblk)
+{
+    constexpr int CH = CINP / 8;
+    constexpr int XI = 36 * 5 * CH, DI = 16 * 4 * 4;  // staging items: 4 voxels x 8 channels
+    __shared__ __align__(16) unsigned int sX[CINP * kXStr];
+    __shared__ __align__(16) unsigned int sD[32 * kDStr];
+    const int tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int lr = lane & 31, lh = lane >> 5;
+    const int dy = w % 3, dz = w / 3;  // row offsets within the halo (0..2)
+    const unsigned int ntx = (unsigned int)g.nx / 16u;
+    f16v acc[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+    float bs = 0.f;  // bias gradient of channel lr over the rows this wave adds up
+
+    // this thread's staging items of a block: loaded while the block before multiplies
+    constexpr int NI = (XI + DI + kGradThreads - 1) / kGradThreads;
+    u4 v[NI][4];
+    auto fetch = [&](unsigned int blk) {
+        const int x0 = (int)(blk % ntx) * 16, y0 = (int)((blk / ntx) % nty) * 4, z0 = (int)(blk / (ntx * nty)) * 4;
+#pragma unroll
+        for (int m = 0; m < NI; ++m) {
+            const int it = tid + m * kGradThreads;
+            const bool isx = it < XI;
+            const int u = isx ? it : it - XI;
+            const int c = isx ? u % CH : u & 3, gq = isx ? u / CH : u >> 2;
+            const int grp = isx ? gq % 5 : gq & 3, row = isx ? gq / 5 : gq >> 2;
+            const int ly = isx ? row % 6 - 1 : row & 3, lz = isx ? row / 6 - 1 : row >> 2;
+            // rows past the grid's edge carry no gradient: D is zero there, X any row
+            const bool live = isx || (u < DI && y0 + ly < g.ny && z0 + lz < g.nz);
+            const unsigned int line = ((unsigned int)wrapn(z0 + lz, g.nz) * (unsigned int)g.ny +
+                                       (unsigned int)wrapn(y0 + ly, g.ny)) * (unsigned int)g.nx;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int xi = grp * 4 + j;
+                v[m][j] = u4{0u, 0u, 0u, 0u};
+                if (isx) {
+                    if (xi < 18)
+                        v[m][j] = *reinterpret_cast<const u4*>(
+                            X + (size_t)(line + (unsigned int)wrap1(x0 + xi - 1, g.nx)) * CINP + c * 8);
+                } else if (live) {
+                    v[m][j] = *reinterpret_cast<const u4*>(D + (size_t)(line + (unsigned int)(x0 + xi)) * kNPad + c * 8);
                 }
             }
         }
-    }
-}
-
-// dW[t][k][nn] += sum_v X[v + off(t)][k] D[v][nn] over a chunk of voxels per wavefront,
-// added into the canonical FP32 gradient of the layer (k < cin, nn < cout only).
-template <int CINP>
-__global__ __launch_bounds__(kThreads) void k_wgrad(Geo g, const bf16_t* __restrict__ X, const bf16_t* __restrict__ D,
-                                                    float* __restrict__ G, int cin, int cout, unsigned int vchunk)
-{
-    const int lane = threadIdx.x & 63;
-    const unsigned int wid = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-    const int t = (int)(wid % 27u);
-    const unsigned int vbeg = (wid / 27u) * vchunk;
-    const unsigned int n = (unsigned int)g.n;
-    if (vbeg >= n) return;
-    const unsigned int vend = vbeg + vchunk < n ? vbeg + vchunk : n;
-    const int lr = lane & 15, lk = (lane >> 4) * 4;
-    f4 acc[CINP / 16][2];
+    };
+    auto stage = [&]() {
 #pragma unroll
-    for (int mb = 0; mb < CINP / 16; ++mb)
+        for (int m = 0; m < NI; ++m) {
+            const int it = tid + m * kGradThreads;
+            if (it >= XI + DI) continue;
+            const bool isx = it < XI;
+            const int u = isx ? it : it - XI;
+            const int c = isx ? u % CH : u & 3, gq = isx ? u / CH : u >> 2;
+            const int grp = isx ? gq % 5 : gq & 3, row = isx ? gq / 5 : gq >> 2;
+            uint2 q[8];
+            transpose_8x4(v[m], q);
+            unsigned int* dst = isx ? sX + (c * 8) * kXStr + row * kXRow + grp * 2 : sD + (c * 8) * kDStr + row * 8 + grp * 2;
+            const int str = isx ? kXStr : kDStr;
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
-    for (unsigned int vb = vbeg; vb < vend; vb += 16) {
-        unsigned int vx[4];
-        unsigned int vd[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const unsigned int v = vb + lk + j;  // < vend: chunks are multiples of 16 and n is too
-            vd[j] = v;
-            const int x = (int)(v % (unsigned int)g.nx), y = (int)((v / (unsigned int)g.nx) % (unsigned int)g.ny);
-            const int z = (int)(v / ((unsigned int)g.nx * (unsigned int)g.ny));
-            vx[j] = tap_voxel(g, x, y, z, t);
+            for (int k = 0; k < 8; ++k) *reinterpret_cast<uint2*>(dst + k * str) = q[k];
         }
-        s4 a[CINP / 16], b[2];
+    };
+    fetch(blockIdx.x);  // the grid has at most nblk workgroups
+    for (unsigned int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+        __syncthreads();  // the block before is read
+        stage();
+        __syncthreads();
+        if (blk + gridDim.x < nblk) fetch(blk + gridDim.x);
+        const bool rows = CINP >= 32 || lr < CINP;
+        const unsigned int* xa = sX + (rows ? lr : 0) * kXStr + lh * 4;
+        const unsigned int* da = sD + lr * kDStr + lh * 4;
+#pragma unroll 2
+        for (int r = 0; r < 16; ++r) {
+            const unsigned int* xr = xa + ((dz + (r >> 2)) * 6 + dy + (r & 3)) * kXRow;
+            uint2 p0 = *reinterpret_cast<const uint2*>(xr), p1 = *reinterpret_cast<const uint2*>(xr + 2);
+            unsigned int p2 = xr[4];
+            if (!rows) p0 = p1 = uint2{0u, 0u}, p2 = 0u;
+            const u4 b = *reinterpret_cast<const u4*>(da + r * 8);
+            const u4 am = {p0.x, p0.y, p1.x, p1.y}, ap = {p0.y, p1.x, p1.y, p2};
+            u4 a0;
 #pragma unroll
-        for (int mb = 0; mb < CINP / 16; ++mb)
+            for (int j = 0; j < 4; ++j) a0[j] = __builtin_amdgcn_alignbit(ap[j], am[j], 16);
+            if (r % kGradWaves == w) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) a[mb][j] = (short)X[(size_t)vx[j] * CINP + mb * 16 + lr];
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[nb][j] = (short)D[(size_t)vd[j] * kNPad + nb * 16 + lr];
-#pragma unroll
-        for (int mb = 0; mb < CINP / 16; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-                acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[mb], b[nb], acc[mb][nb], 0, 0, 0);
-    }
-#pragma unroll
-    for (int mb = 0; mb < CINP / 16; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int k = mb * 16 + lk + i, nn = nb * 16 + lr;
-                if (k < cin && nn < cout) atomicAdd(&G[((size_t)t * cin + k) * cout + nn], acc[mb][nb][i]);
+                for (int j = 0; j < 4; ++j) bs += __uint_as_float(b[j] << 16) + __uint_as_float(b[j] & 0xffff0000u);
             }
+            const bf8 bb = __builtin_bit_cast(bf8, b);
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, am), bb, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a0), bb, acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, ap), bb, acc[2], 0, 0, 0);
+        }
+    }
+    // the partial in the layout of the layer's parameters: W [27][cin][cout], b [cout];
+    // accumulator element i of lane l: row (k) 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
+    float* o = part + (size_t)blockIdx.x * ((size_t)27 * cin * cout + cout);
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int k = (i >> 2) * 8 + lh * 4 + (i & 3);
+            if (k < cin && lr < cout) o[((size_t)(w * 3 + t) * cin + k) * cout + lr] = acc[t][i];
+        }
+    // bias: the waves' and half-waves' sums of a channel through LDS
+    __syncthreads();
+    float* sb = reinterpret_cast<float*>(sD);  // [wave][half][channel]
+    sb[tid] = bs;
+    __syncthreads();
+    if (tid < cout) {
+        float t = 0.f;
+        for (int q = 0; q < 2 * kGradWaves; ++q) t += sb[q * 32 + tid];
+        o[(size_t)27 * cin * cout + tid] = t;
+    }
 }
 
-// db[nn] += sum_v D[v][nn]
-__global__ __launch_bounds__(kThreads) void k_bgrad(Geo g, const bf16_t* __restrict__ D, float* __restrict__ G, int cout)
+// G[e] += sum over the np partials of part[.][e], in FP64 and in a fixed order: 64
+// gradients per workgroup, the partials split over its four waves.
+__global__ __launch_bounds__(kThreads) void k_grad_sum(const float* __restrict__ part, unsigned int ne, int np,
+                                                       float* __restrict__ G)
 {
-    __shared__ float s[kThreads];
-    const int nn = threadIdx.x & 31, part = threadIdx.x >> 5;  // 8 voxel lanes per channel
-    float acc = 0.f;
-    const unsigned int n = (unsigned int)g.n;
-    for (unsigned int v = blockIdx.x * 8 + part; v < n; v += gridDim.x * 8) acc += bf2f(D[(size_t)v * kNPad + nn]);
-    s[threadIdx.x] = acc;
-    __syncthreads();
-    if (part == 0 && nn < cout) {
-        float t = 0.f;
-        for (int q = 0; q < 8; ++q) t += s[q * 32 + nn];
-        atomicAdd(&G[nn], t);
+    __shared__ double s[kThreads];
+    const unsigned int e = blockIdx.x * 64 + (threadIdx.x & 63);
+    double t = 0.0;
+    if (e < ne) {
+        const float* p = part + e;
+#pragma unroll 8
+        for (int q = (int)(threadIdx.x >> 6); q < np; q += 4) t += (double)p[(size_t)q * ne];
     }
+    s[threadIdx.x] = t;
+    __syncthreads();
+    if (threadIdx.x < 64 && e < ne)
+        G[e] += (float)((s[threadIdx.x] + s[threadIdx.x + 64]) + (s[threadIdx.x + 128] + s[threadIdx.x + 192]));
 }
 
 // The closure in flux and constrained-transport form: the corrected value of field q of
@@ -524,19 +592,23 @@ __global__ __launch_bounds__(kThreads) void k_closure_check(Geo g, const float* 
     if (threadIdx.x == 0) partial[blockIdx.x] = bad ? -1.0 : INFINITY;
 }
 
-// rw[f][c] = 2 w_f (P - T) / n and the loss partial sum_f w_f (P - T)^2 / n per block.
-__global__ __launch_bounds__(kThreads) void k_residual(Geo g, const double* __restrict__ P, const double* __restrict__ T,
-                                                       const float* __restrict__ w8, float* __restrict__ RW,
-                                                       double* __restrict__ partial)
+// With P the corrected value of the state U (k_closure_apply's, formed here instead of
+// stored and read back): rw[f][c] = 2 w_f (P - T) / n and the loss partial
+// sum_f w_f (P - T)^2 / n per block.
+__global__ __launch_bounds__(kThreads) void k_residual(Geo g, const float* __restrict__ O, const float* __restrict__ sF,
+                                                       float sE, double dt, const double* __restrict__ U,
+                                                       const double* __restrict__ T, const float* __restrict__ w8,
+                                                       float* __restrict__ RW, double* __restrict__ partial)
 {
     __shared__ double s[kThreads / 64];
     const unsigned int c = blockIdx.x * kThreads + threadIdx.x;
     const unsigned int n = (unsigned int)g.n;
     double l = 0.0;
     if (c < n) {
+        const CorrIdx k = corr_idx(g, c);
 #pragma unroll
         for (int f = 0; f < 8; ++f) {
-            const double r = P[(size_t)f * n + c] - T[(size_t)f * n + c];
+            const double r = corrected(g, O, sF, sE, dt, U, k, f) - T[(size_t)f * n + c];
             RW[(size_t)f * n + c] = (float)(2.0 * w8[f] * r / (double)n);
             l += w8[f] * r * r / (double)n;
         }
@@ -559,7 +631,8 @@ __global__ __launch_bounds__(kThreads) void k_out_grad(Geo g, const float* __res
     const int z = (int)(c / ((unsigned int)g.nx * (unsigned int)g.ny));
     // c - e_d
     const unsigned int cm[3] = {tap_voxel(g, x, y, z, 12), tap_voxel(g, x, y, z, 10), tap_voxel(g, x, y, z, 4)};
-    bf16_t* o = D + (size_t)c * kNPad;
+    // the voxel's 32 channels leave as four 16-byte stores
+    bf16_t o[kNPad];
     // dF_fd[c] enters u_f[c] with +dt/dx_d and u_f[c - e_d] with -dt/dx_d
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
@@ -577,6 +650,13 @@ __global__ __launch_bounds__(kThreads) void k_out_grad(Geo g, const float* __res
     o[17] = f2bf((float)(sE * (dd(gx, 1) - dd(gy, 0))));
 #pragma unroll
     for (int q = 18; q < kNPad; ++q) o[q] = 0;
+    uint4* d4 = reinterpret_cast<uint4*>(D + (size_t)c * kNPad);
+#pragma unroll
+    for (int q = 0; q < kNPad / 8; ++q) {
+        const bf16_t* h = o + 8 * q;
+        d4[q] = uint4{h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16, h[4] | (uint32_t)h[5] << 16,
+                      h[6] | (uint32_t)h[7] << 16};
+    }
 }
 
 // BF16 weight copies of layer l from the FP32 master: forward Wf[t][nn][k] = W[t][k][nn];
@@ -659,8 +739,8 @@ struct mhd_cnn {
     float* O;                // output channels [18][n]
     bf16_t *D0, *D1;         // backward gradients [n][32]
     float* RW;               // weighted residual [8][n]
-    double* Pred;            // corrected prediction [8][n]
     double* partial;
+    float* gpart;            // gradient partials, one layer at a time
     float* scal;             // mu[8], sd[8], sF[5], w8[8]
     float sE;
     unsigned int nblk;
@@ -671,8 +751,15 @@ namespace {
 size_t ca(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct CLayout {
-    size_t params, wf[kLayers], wb[kLayers], a[kLayers], o, d, rw, pred, partial, scal, total;
+    size_t params, wf[kLayers], wb[kLayers], a[kLayers], o, d, rw, partial, gpart, scal, total;
 };
+
+// Blocks of 16 x 4 x 4 voxels of the gradient kernel and the workgroups that share them.
+unsigned int grad_blocks(int nx, int ny, int nz)
+{
+    return (unsigned int)(nx / 16) * (unsigned int)((ny + 3) / 4) * (unsigned int)((nz + 3) / 4);
+}
+unsigned int grad_groups(unsigned int nblk) { return nblk < (unsigned int)kGradGroups ? nblk : (unsigned int)kGradGroups; }
 
 CLayout clayout(const mhd_grid* g)
 {
@@ -687,10 +774,10 @@ CLayout clayout(const mhd_grid* g)
     L.o = ca(n * 18 * sizeof(float));
     L.d = ca(n * kNPad * sizeof(bf16_t));
     L.rw = ca(n * 8 * sizeof(float));
-    L.pred = ca(n * 8 * sizeof(double));
     L.partial = ca(((n + kThreads - 1) / kThreads + 1) * sizeof(double));  // + the closure's flag
+    L.gpart = ca((size_t)grad_groups(grad_blocks(g->nx, g->ny, g->nz)) * layer_params(1) * sizeof(float));
     L.scal = ca(64 * sizeof(float));
-    L.total = 4 * L.params + L.o + 2 * L.d + L.rw + L.pred + L.partial + L.scal;
+    L.total = 4 * L.params + L.o + 2 * L.d + L.rw + L.partial + L.gpart + L.scal;
     for (int l = 0; l < kLayers; ++l) L.total += L.wf[l] + L.wb[l] + L.a[l];
     return L;
 }
@@ -709,12 +796,6 @@ mhd_status cvalidate(const mhd_grid* g, const mhd_physics* p)
 
 mhd_status cdev(hipError_t e) { return e == hipSuccess ? MHD_OK : MHD_E_DEVICE; }
 
-unsigned int conv_blocks(const mhd_cnn* c)
-{
-    const unsigned int waves = (unsigned int)((c->g.n + kVoxPerWave - 1) / kVoxPerWave);
-    return (waves + 3) / 4;
-}
-
 hipError_t pack_all(mhd_cnn* c)
 {
     for (int l = 0; l < kLayers; ++l) {
@@ -725,25 +806,16 @@ hipError_t pack_all(mhd_cnn* c)
     return hipGetLastError();
 }
 
-// One convolution launch: the LDS-staged kernel where the grid tiles into 16 x 4 x 8 or
-// 16 x 4 x 4 blocks, else the per-tap gather kernel (all give the same bits).
+// One convolution launch.
 template <int CINP, int MODE>
 void conv(const mhd_cnn* c, const bf16_t* X, const bf16_t* B, const float* bias, const bf16_t* M, bf16_t* Y,
           float* O, int nstore)
 {
-    if (c->g.ny % kTileY == 0 && c->g.nz % 8 == 0) {
-        // 16 x 4 x 8 blocks, two planes per wavefront (78 KB of LDS: two workgroups per CU)
-        const unsigned int nblk = (unsigned int)(c->g.n / (16 * kTileY * 8));
-        hipLaunchKernelGGL((k_conv_lds<CINP, MODE, 2>), dim3(nblk), dim3(kThreads), 0, c->stream, c->g, X, B, bias,
-                           M, Y, O, nstore);
-    } else if (c->g.ny % kTileY == 0 && c->g.nz % 4 == 0) {
-        const unsigned int nblk = (unsigned int)(c->g.n / (16 * kTileY * 4));
-        hipLaunchKernelGGL((k_conv_lds<CINP, MODE, 1>), dim3(nblk), dim3(kThreads), 0, c->stream, c->g, X, B, bias,
-                           M, Y, O, nstore);
-    } else {
-        hipLaunchKernelGGL((k_conv<CINP, MODE>), dim3(conv_blocks(c)), dim3(kThreads), 0, c->stream, c->g, X, B,
-                           bias, M, Y, O, nstore);
-    }
+    const unsigned int nty = (unsigned int)((c->g.ny + kTileY - 1) / kTileY);
+    const unsigned int nblk = (unsigned int)(c->g.nx / 16) * nty * (unsigned int)((c->g.nz + kTileZ - 1) / kTileZ);
+    const unsigned int grid = nblk < (unsigned int)kConvGroups ? nblk : (unsigned int)kConvGroups;
+    hipLaunchKernelGGL((k_conv<CINP, MODE>), dim3(grid), dim3(kConvThreads), 0, c->stream, c->g, X, B, bias, M, Y, O,
+                       nstore, nty, nblk);
 }
 
 // forward pass from a canonical state; keeps every layer input for the backward pass
@@ -833,8 +905,8 @@ mhd_status mhd_cnn_create(const mhd_grid* grid, const mhd_physics* phys, void* w
     c->D0 = (bf16_t*)p; p += L.d;
     c->D1 = (bf16_t*)p; p += L.d;
     c->RW = (float*)p; p += L.rw;
-    c->Pred = (double*)p; p += L.pred;
     c->partial = (double*)p; p += L.partial;
+    c->gpart = (float*)p; p += L.gpart;
     c->scal = (float*)p;
     c->sE = 1.0f;
     // zero parameters, moments and gradients; unit normalisation
@@ -931,31 +1003,28 @@ mhd_status mhd_cnn_accumulate(mhd_cnn* c, const double* state_t, const double* c
                               double dt, double* loss)
 {
     if (!c || !state_t || !coarse_next || !target || !(dt > 0.0) || !std::isfinite(dt)) return MHD_E_INVAL;
-    const size_t nb = (size_t)c->g.n * 8 * sizeof(double);
     hipError_t e = forward(c, state_t);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->Pred, coarse_next, nb, hipMemcpyDeviceToDevice, c->stream);
-    if (e == hipSuccess) e = apply(c, dt, c->Pred);
     if (e != hipSuccess) return MHD_E_DEVICE;
-    hipLaunchKernelGGL(k_residual, dim3(c->nblk), dim3(kThreads), 0, c->stream, c->g, c->Pred, target, c->scal + 24,
-                       c->RW, c->partial);
+    hipLaunchKernelGGL(k_residual, dim3(c->nblk), dim3(kThreads), 0, c->stream, c->g, c->O, c->scal + 16, c->sE, dt,
+                       coarse_next, target, c->scal + 24, c->RW, c->partial);
     hipLaunchKernelGGL(k_out_grad, dim3(c->nblk), dim3(kThreads), 0, c->stream, c->g, c->RW, c->scal + 16, c->sE, dt,
                        c->D0);
     // backward: layer l consumes D (its output gradient) and A[l] (its input)
     const dim3 bl(kThreads);
-    const unsigned int vchunk = 1024;
-    const unsigned int wwaves = 27u * (unsigned int)((c->g.n + vchunk - 1) / vchunk);
-    const dim3 gw((wwaves + 3) / 4);
-    const unsigned int bblk = 256;
+    const unsigned int gblk = grad_blocks(c->g.nx, c->g.ny, c->g.nz), ng = grad_groups(gblk);
+    const unsigned int gty = (unsigned int)((c->g.ny + 3) / 4);
     bf16_t* D = c->D0;
     bf16_t* Dn = c->D1;
     for (int l = kLayers - 1; l >= 0 && e == hipSuccess; --l) {
-        float* Gw = c->G + param_offset(l);
-        float* Gb = Gw + layer_w(l);
         if (l == 0)
-            hipLaunchKernelGGL((k_wgrad<16>), gw, bl, 0, c->stream, c->g, c->A[0], D, Gw, kCin[l], kCout[l], vchunk);
+            hipLaunchKernelGGL((k_grad<16>), dim3(ng), dim3(kGradThreads), 0, c->stream, c->g, c->A[0], D, c->gpart,
+                               kCin[l], kCout[l], gty, gblk);
         else
-            hipLaunchKernelGGL((k_wgrad<32>), gw, bl, 0, c->stream, c->g, c->A[l], D, Gw, kCin[l], kCout[l], vchunk);
-        hipLaunchKernelGGL(k_bgrad, dim3(bblk), bl, 0, c->stream, c->g, D, Gb, kCout[l]);
+            hipLaunchKernelGGL((k_grad<32>), dim3(ng), dim3(kGradThreads), 0, c->stream, c->g, c->A[l], D, c->gpart,
+                               kCin[l], kCout[l], gty, gblk);
+        const unsigned int ne = (unsigned int)layer_params(l);
+        hipLaunchKernelGGL(k_grad_sum, dim3((ne + 63) / 64), bl, 0, c->stream, c->gpart, ne, (int)ng,
+                           c->G + param_offset(l));
         if (l > 0) {
             // gradient of layer l's input, through the ReLU of layer l-1 (mask = A[l] > 0)
             conv<32, 2>(c, D, c->Wb[l], nullptr, c->A[l], Dn, nullptr, 0);
