@@ -100,7 +100,14 @@ __device__ __forceinline__ R slope_vl(R am, R a0, R ap)
 #pragma clang fp contract(off)
     const R dm = a0 - am, dp = ap - a0;
     const R pr = dm * dp;
-    return pr > R(0) ? div_r(R(2) * pr, dm + dp) : R(0);
+    if constexpr (sizeof(R) == 8) {
+        // 0 / 1 where the slope is zero: a select on the quotient compiles to a divergent
+        // branch around the division, which few waves can skip
+        const R den = pr > R(0) ? dm + dp : R(1);
+        return div_r(R(2) * max_r(pr, R(0)), den);
+    } else {
+        return pr > R(0) ? div_r(R(2) * pr, dm + dp) : R(0);
+    }
 }
 
 // Colella-Woodward limited central slope of the middle cell.
