@@ -17,14 +17,16 @@
 // exact, O(N) and momentum conserving.
 //
 // Each stage is two launches:
-//   k_fluid_pass  one workgroup = one fluid on a 64 x 4 tile of xy columns marching a
-//                 chunk of z planes.  The fluid's primitives of the current plane and
-//                 its x/y halo are staged in LDS (double buffered: the loads of plane
-//                 k+1 are issued before plane k is computed), the z stencil of each
-//                 column is a register pipeline that carries the flux of the low z
-//                 face.  Every cell solves the Riemann problems on both of its x and y
-//                 faces (no flux array, no extra barrier) and writes the explicit part
-//                 of its stage:
+//   k_fluid_pass  one wave = one fluid on a tile of 64 columns x 1 or 2 rows marching a
+//                 chunk of z planes; waves share nothing and there is no barrier.  A lane
+//                 owns a column of each row: the z stencil is a register pipeline that
+//                 carries the flux of the low z face, the y stencil the tile's rows (held
+//                 by the pipelines) and the rows beside them, the x stencil the row in the
+//                 wave's own LDS.  Every low x face is solved by one lane, which hands its
+//                 flux to the lane on its left; the two faces at the tile's edge of all
+//                 rows are solved together in one more pass.  A face is solved once per
+//                 direction within a tile (x: 1 + 1/rows per cell, y: 1 + 1/rows, z: 1)
+//                 and a cell's slope once, and each stage's explicit part is written:
 //                   stage 1: X = u + h L(u);  stage 2: X = cu u + c1 U1 + cf L(U1).
 //                 Densities are final after this pass (drag moves only momentum).
 //   k_drag        pointwise: adds the stage-1 drag rates (stage 2), solves S_h for the
@@ -40,11 +42,20 @@
 namespace mhd {
 
 namespace {
-constexpr double kLam = 1.7071067811865475244;    // 1 + 1/sqrt(2)
+constexpr double kLam = 1.7071067811865475244;     // 1 + 1/sqrt(2)
 constexpr double kDelta = 0.70710678118654752440;  // 1 - 1/(2 lam) = 1/sqrt(2)
 
-constexpr int DTX = 64;  // lanes along x
-constexpr int DTY = 4;   // waves along y
+constexpr int DTX = 64;    // lanes along x
+constexpr int DWAVES = 4;  // waves of a workgroup (independent of each other)
+
+// Orders one wave's LDS writes before its other lanes' reads (and the reads before the
+// next writes): LDS serves a wave's accesses in order, only the compiler has to keep it.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
 
 // Blocks are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of work
 // items so neighbouring tiles of one fluid share an L2.
@@ -79,34 +90,16 @@ struct Halo {
     static constexpr int H = RECON == 0 ? 1 : 2;
 };
 
-// States on the low face (lo) and high face (hi) of the middle cell of a[0..2H]:
-// donor cell or van Leer-limited PLM, the same formula on every face.
-template <int RECON, class R>
-__device__ __forceinline__ void both_faces(const R* a, R& loL, R& loR, R& hiL, R& hiR)
-{
-    if constexpr (RECON == 0) {
-        loL = a[0]; loR = a[1]; hiL = a[1]; hiR = a[2];
-    } else {
-        const R sm = slope_vl(a[0], a[1], a[2]);
-        const R s0 = slope_vl(a[1], a[2], a[3]);
-        const R sp = slope_vl(a[2], a[3], a[4]);
-        loL = a[1] + R(0.5) * sm;
-        loR = a[2] - R(0.5) * s0;
-        hiL = a[2] + R(0.5) * s0;
-        hiR = a[3] - R(0.5) * sp;
-    }
-}
-
 // Face flux along direction D from the global-frame states; returns global-frame
 // components (mass, Mx, My, Mz).
-template <int D, class R>
-__device__ __forceinline__ void face_flux(bool gas, R cs, const R L[4], const R Rs[4], R out[4])
+template <int D, bool GAS, class R>
+__device__ __forceinline__ void face_flux(R cs, const R L[4], const R Rs[4], R out[4])
 {
     constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
     const Prim4<R> l{L[0], L[1 + D], L[1 + T1], L[1 + T2]};
     const Prim4<R> r{Rs[0], Rs[1 + D], Rs[1 + T1], Rs[1 + T2]};
     Flux4<R> f;
-    if (gas)
+    if constexpr (GAS)
         riemann_iso_hlle(l, r, cs, f);
     else
         riemann_dust(l, r, f);
@@ -133,7 +126,8 @@ struct PassArgs {
 
 // z reconstruction of one variable of one column as a pipeline over the planes the
 // column visits: push(plane m + 1 + AHEAD) returns the two states on the face m + 1/2
-// (one slope per plane for PLM).
+// (one slope per plane for PLM).  Between the pushes of planes m + AHEAD and m + 1 + AHEAD
+// here() is the value of plane m.
 template <int RECON, class R>
 struct ZLine;
 template <class R>
@@ -141,6 +135,7 @@ struct ZLine<0, R> {
     static constexpr int AHEAD = 0, PRIME = 1;
     R prev;
     __device__ void prime(const R* a) { prev = a[0]; }
+    __device__ R here() const { return prev; }
     __device__ void push(R a, R& aL, R& aR)
     {
         aL = prev;
@@ -158,6 +153,7 @@ struct ZLine<1, R> {
         am = a[1];
         a0 = a[2];
     }
+    __device__ R here() const { return am; }
     __device__ void push(R a, R& aL, R& aR)
     {
         const R d = slope_vl(am, a0, a);
@@ -169,66 +165,93 @@ struct ZLine<1, R> {
     }
 };
 
-template <int RECON, int STAGE, class R>
-__global__ __launch_bounds__(DTX* DTY) void k_fluid_pass(Geo g, DustParams p, PassArgs<R> a, int kz,
-                                                           unsigned int ntx, unsigned int nty,
-                                                           unsigned int ntiles, unsigned int nblk)
+// Value of the lane on the left / right of a wavefront (the first / last lane: `edge`).
+__device__ __forceinline__ float lane_left(float v, float edge)
 {
-    constexpr int H = Halo<RECON>::H, W = 2 * H + 1;
-    constexpr int LX = DTX + 2 * H, LY = DTY + 2 * H;
-    constexpr int NT = DTX * DTY, NI = (LX * LY + NT - 1) / NT;  // staging items per thread
-    using Z = ZLine<RECON, R>;
-    __shared__ R sw[2][4][LY][LX];  // primitives of plane k (and k+1 being staged)
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_right(float v, float edge)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double lane_left(double v, double edge)
+{
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(v), 0x138, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(v), 0x138, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_right(double v, double edge)
+{
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(v), 0x130, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(v), 0x130, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
 
-    const unsigned int item = xcd_item(blockIdx.x, nblk);
-    const int s = (int)(item / ntiles);  // fluid: 0 gas, 1.. dust
-    const unsigned int t = item - (unsigned int)s * ntiles;
-    const bool gas = s == 0;
-    const int x0 = (int)(t % ntx) * DTX;
-    const int y0 = (int)((t / ntx) % nty) * DTY;
-    const int k0 = (int)(t / (ntx * nty)) * kz;
-    const int k1 = min(k0 + kz, g.nz);
-    const int lane = threadIdx.x & 63, row = threadIdx.x >> 6;
-    const int i = x0 + lane, j = y0 + row;
-    const bool live = i < g.nx && j < g.ny;
-    const int ic = live ? i : 0, jc = live ? j : 0;
+// States of a cell on its low and high face from the cell and its two neighbours.
+template <int RECON, class R>
+__device__ __forceinline__ void cell_states(R am, R a0, R ap, R& lo, R& hi)
+{
+    if constexpr (RECON == 0) {
+        lo = hi = a0;
+    } else {
+        const R s = slope_vl(am, a0, ap);
+        lo = fma_r(R(-0.5), s, a0);
+        hi = fma_r(R(0.5), s, a0);
+    }
+}
+
+template <int RECON, class R, int NR>
+struct PassLds {
+    static constexpr int LX = DTX + 2 * Halo<RECON>::H;
+    R row[NR][4][LX];  // primitives of the wave's rows with their x halo
+    R edge[NR][2][4];  // high-side state of column x0 - 1, flux through face x0 + 63 1/2
+};
+
+// One wave's tile of fluid s (GAS: the gas, else a dust species; a template argument so
+// that the faces of a cell are one straight block).  Bound by its arithmetic and its
+// latency at two (FP64) and three (FP32) waves per SIMD; 192^3, 8 species, PLM, stage 1 /
+// stage 2: FP64 2.28 / 2.41 -> 1.65 / 1.76 ms, FP32 0.98 / 1.03 -> 0.83 / 0.87 ms against
+// a workgroup of four waves on 64 x 4 columns that staged the tile with its halo in
+// double-buffered LDS and solved both faces of every cell in x and y (five Riemann
+// problems and seven slopes per variable and cell; here four and five).  Four rows need
+// more registers than two waves per SIMD leave (FP64 spills: 3.7 ms; FP32 0.96 ms).
+template <int RECON, int STAGE, class R, int NR, bool GAS>
+__device__ __forceinline__ void fluid_tile(const Geo& g, const DustParams& p, const PassArgs<R>& a, int s, int x0,
+                                           int y0, int k0, int k1, PassLds<RECON, R, NR>& lds)
+{
+    // every rounding is written out: a cell's update does not depend on the tiling
+#pragma clang fp contract(off)
+    constexpr int H = Halo<RECON>::H, NX = NR * 2 * H;
+    static_assert(NX <= 64, "one lane per cell of the x halo");
+    using Z = ZLine<RECON, R>;
+    const int lane = (int)threadIdx.x & 63;
+    const int i = x0 + lane;
+    const bool live = i < g.nx;
+    // columns and rows past the grid's edge are the periodic ones
+    const unsigned int col = (unsigned int)wrap_any(i, g.nx);
     const long long n = g.n;
     const unsigned int plane = (unsigned int)g.nx * (unsigned int)g.ny;
-    const R* f[4];
+    auto rowoff = [&](int r) { return (unsigned int)wrap_any(y0 + r, g.ny) * (unsigned int)g.nx; };
+    const R *f[4], *b[4];
     R* o[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         f[q] = a.src + (4LL * s + q) * n;
+        b[q] = a.base + (4LL * s + q) * n;
         o[q] = a.out + (4LL * s + q) * n;
     }
-    const R* b0 = a.base + 4LL * s * n;
     const R cs = R(p.cs);
     const R rho_floor = R(p.rho_floor), dust_floor = R(p.dust_floor);
     const R gx3[3] = {R(p.gacc[0]), R(p.gacc[1]), R(p.gacc[2])};
     const R hr = R(a.h), cur_ = R(a.cu), c1r = R(a.c1);
     const R idx[3] = {R(g.inv_dx[0]), R(g.inv_dx[1]), R(g.inv_dx[2])};
-    const unsigned int col = (unsigned int)jc * g.nx + ic;
 
-    // this thread's staging items of a plane (tile + x/y halo, corners skipped)
-    unsigned int soff[NI];
-    int sr[NI], sc[NI];
-    bool sv[NI];
-#pragma unroll
-    for (int m = 0; m < NI; ++m) {
-        const int q = threadIdx.x + m * NT;
-        sr[m] = q / LX;
-        sc[m] = q - sr[m] * LX;
-        const bool xh = sc[m] < H || sc[m] >= H + DTX, yh = sr[m] < H || sr[m] >= H + DTY;
-        sv[m] = q < LX * LY && !(xh && yh);
-        const int gx = wrap_any(x0 + sc[m] - H, g.nx), gy = wrap_any(y0 + sr[m] - H, g.ny);
-        soff[m] = sv[m] ? (unsigned int)gy * g.nx + gx : 0u;
-    }
     // primitives from the raw state: the gas density is floored; a dust species below
     // its floor reads as the floor at rest
     auto prim_of = [&](const R raw[4], R w[4]) {
-        const bool rest = !gas && raw[0] < dust_floor;
+        const bool rest = !GAS && raw[0] < dust_floor;
         R d = raw[0];
-        if (gas && d < rho_floor) d = rho_floor;
+        if (GAS && d < rho_floor) d = rho_floor;
         const R id = rcp(d);
         w[0] = rest ? dust_floor : d;
         w[1] = rest ? R(0) : raw[1] * id;
@@ -239,127 +262,202 @@ __global__ __launch_bounds__(DTX* DTY) void k_fluid_pass(Geo g, DustParams p, Pa
 #pragma unroll
         for (int q = 0; q < 4; ++q) raw[q] = ld(f[q], c);
     };
-    R raw[NI][4];
-    auto fetch_plane = [&](int kk) {
-        const unsigned int pb = (unsigned int)kk * plane;
-#pragma unroll
-        for (int m = 0; m < NI; ++m)
-            if (sv[m]) load_raw(pb + soff[m], raw[m]);
-    };
-    auto store_plane = [&](int buf) {
-#pragma unroll
-        for (int m = 0; m < NI; ++m)
-            if (sv[m]) {
-                R w[4];
-                prim_of(raw[m], w);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) sw[buf][v][sr[m]][sc[m]] = w[v];
-            }
-    };
+    // this lane's cell of the x halo: row xr, column xe of the staged row
+    const int xr = lane / (2 * H), xc = lane % (2 * H), xe = xc < H ? xc : DTX + xc;
+    const unsigned int xoff = lane < NX ? (unsigned int)wrap_any(y0 + xr, g.ny) * (unsigned int)g.nx +
+                                              (unsigned int)wrap_any(x0 + xe - H, g.nx)
+                                        : 0u;
 
-    // z pipeline of the own column, primed so that the first push yields face k0 - 1/2
-    Z zl[4];
-    {
+    // z pipelines of the own columns, primed so that the first push yields face k0 - 1/2
+    Z zl[NR][4];
+    R fzlo[NR][4];  // z flux on the low face of the current cell
+    R zraw[NR][4];  // raw state of the next plane the z pipeline takes
+    R xraw[4];      // raw x halo of the current plane
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
         R pre[4][Z::PRIME];
 #pragma unroll
         for (int m = 0; m < Z::PRIME; ++m) {
             R r4[4], w[4];
-            load_raw((unsigned int)wrap_any(k0 - Z::PRIME + Z::AHEAD + m, g.nz) * plane + col, r4);
+            load_raw((unsigned int)wrap_any(k0 - Z::PRIME + Z::AHEAD + m, g.nz) * plane + rowoff(r) + col, r4);
             prim_of(r4, w);
 #pragma unroll
             for (int v = 0; v < 4; ++v) pre[v][m] = w[v];
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) zl[v].prime(pre[v]);
-    }
-    R zraw[4];  // raw state of the next plane the z pipeline takes
-    load_raw((unsigned int)wrap_any(k0 + Z::AHEAD, g.nz) * plane + col, zraw);
-    R fzlo[4];  // z flux on the low face of the current cell
-    {
+        for (int v = 0; v < 4; ++v) zl[r][v].prime(pre[v]);
+        load_raw((unsigned int)wrap_any(k0 + Z::AHEAD, g.nz) * plane + rowoff(r) + col, zraw[r]);
         R w[4], L[4], Rr[4];
-        prim_of(zraw, w);
+        prim_of(zraw[r], w);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) zl[v].push(w[v], L[v], Rr[v]);
-        face_flux<2>(gas, cs, L, Rr, fzlo);
+        for (int v = 0; v < 4; ++v) zl[r][v].push(w[v], L[v], Rr[v]);
+        face_flux<2, GAS>(cs, L, Rr, fzlo[r]);
+        load_raw((unsigned int)wrap_any(k0 + 1 + Z::AHEAD, g.nz) * plane + rowoff(r) + col, zraw[r]);
     }
-    load_raw((unsigned int)wrap_any(k0 + 1 + Z::AHEAD, g.nz) * plane + col, zraw);
-    fetch_plane(k0);
-    store_plane(k0 & 1);
-    __syncthreads();
+    if (lane < NX) load_raw((unsigned int)k0 * plane + xoff, xraw);
 
     for (int k = k0; k < k1; ++k) {
-        const int cur = k & 1;
-        // loads for the next plane go out first; they land while this plane computes
         const bool more = k + 1 < k1;
-        if (more) fetch_plane(k + 1);
-        const unsigned int c = (unsigned int)k * plane + col;
-        R own[4], ub[4];
-        load_raw(c, own);
-        if constexpr (STAGE == 2) {
+        const unsigned int pb = (unsigned int)k * plane;
+        wave_sync();  // the plane below is read
+        R hraw[2 * H][4];  // the rows below and above the tile, needed after the edge faces
 #pragma unroll
-            for (int v = 0; v < 4; ++v) ub[v] = ld(b0 + v * n, c);
+        for (int m = 0; m < 2 * H; ++m) load_raw(pb + rowoff(m < H ? m - H : NR + m - H) + col, hraw[m]);
+        // ---- the rows of plane k with their x halo
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) lds.row[r][v][lane + H] = zl[r][v].here();
+        if (lane < NX) {
+            R w[4];
+            prim_of(xraw, w);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) lds.row[xr][v][xe] = w[v];
         }
-        R zw[4];
-        prim_of(zraw, zw);
-        if (more) load_raw((unsigned int)wrap_any(k + 2 + Z::AHEAD, g.nz) * plane + col, zraw);
+        // the x halo of the next plane goes out first; it lands while this plane computes
+        if (more && lane < NX) load_raw(pb + plane + xoff, xraw);
+        wave_sync();
+        // ---- the edge faces of all rows in one pass: lane 2 r + e the face at x0 + 64 e of row r
+        if (lane < 2 * NR) {
+            const int r = lane >> 1, e = lane & 1;
+            R lo[4], hi[4], fx[4], dum;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const R* q = &lds.row[r][v][e * DTX];
+                if constexpr (RECON == 0) {
+                    hi[v] = q[0];
+                    lo[v] = q[1];
+                } else {
+                    cell_states<RECON, R>(q[0], q[1], q[2], dum, hi[v]);
+                    cell_states<RECON, R>(q[1], q[2], q[3], lo[v], dum);
+                }
+            }
+            face_flux<0, GAS>(cs, hi, lo, fx);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) lds.edge[r][e][v] = e ? fx[v] : hi[v];
+        }
+        wave_sync();
 
-        // acc = ((fx + fy) + fz): flux differences accumulated direction by direction
-        R acc[4];
+        R hv[2 * H][4];
+#pragma unroll
+        for (int m = 0; m < 2 * H; ++m) prim_of(hraw[m], hv[m]);
+        // ---- y: flux through the low face of row 0, then one face per row
+        R hy[4], fy[4];  // high-side state of the row below, flux through the face above it
         {
-            R Lm[4], Rm[4], Lp[4], Rp[4], st5[W], fl[4], fh[4];
+            R lo[4], dum, hm[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-#pragma unroll
-                for (int m = 0; m < W; ++m) st5[m] = sw[cur][v][row + H][lane + m];
-                both_faces<RECON, R>(st5, Lm[v], Rm[v], Lp[v], Rp[v]);
+                if constexpr (RECON == 0) {
+                    hm[v] = hv[0][v];
+                } else {
+                    cell_states<RECON, R>(hv[0][v], hv[1][v], zl[0][v].here(), dum, hm[v]);
+                }
+                const R below = hv[H - 1][v], up = NR > 1 ? zl[NR > 1 ? 1 : 0][v].here() : hv[H][v];
+                cell_states<RECON, R>(below, zl[0][v].here(), up, lo[v], hy[v]);
             }
-            face_flux<0>(gas, cs, Lm, Rm, fl);
-            face_flux<0>(gas, cs, Lp, Rp, fh);
+            face_flux<1, GAS>(cs, hm, lo, fy);
+        }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = (fh[v] - fl[v]) * idx[0];
+        for (int r = 0; r < NR; ++r) {
+            const unsigned int c = pb + rowoff(r) + col;
+            R own[4], ub[4];
+            load_raw(c, own);
+            if constexpr (STAGE == 2) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-#pragma unroll
-                for (int m = 0; m < W; ++m) st5[m] = sw[cur][v][row + m][lane + H];
-                both_faces<RECON, R>(st5, Lm[v], Rm[v], Lp[v], Rp[v]);
+                for (int v = 0; v < 4; ++v) ub[v] = ld(b[v], c);
             }
-            face_flux<1>(gas, cs, Lm, Rm, fl);
-            face_flux<1>(gas, cs, Lp, Rp, fh);
+            // acc = ((fx + fy) + fz): flux differences over the spacings, direction by direction
+            R acc[4];
+            {
+                R lo[4], hi[4], L[4], fl[4], ed[4];
+                const R* e = &lds.edge[r][lane == 63][0];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = acc[v] + (fh[v] - fl[v]) * idx[1];
+                for (int v = 0; v < 4; ++v) {
+                    ed[v] = e[v];
+                    const R* q = &lds.row[r][v][lane + H];
+                    cell_states<RECON, R>(RECON == 0 ? R(0) : q[-1], zl[r][v].here(), RECON == 0 ? R(0) : q[1], lo[v], hi[v]);
+                    L[v] = lane_left(hi[v], ed[v]);
+                }
+                face_flux<0, GAS>(cs, L, lo, fl);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) zl[v].push(zw[v], Lp[v], Rp[v]);
-            face_flux<2>(gas, cs, Lp, Rp, fh);
+                for (int v = 0; v < 4; ++v) acc[v] = lane_right(fl[v], ed[v]) - fl[v];
+            }
+            {
+                R lo[4], hn[4], fn[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                acc[v] = acc[v] + (fh[v] - fzlo[v]) * idx[2];
-                fzlo[v] = fh[v];
+                for (int v = 0; v < 4; ++v) {
+                    // the row above, between row r and the one after it
+                    const R up0 = r + 1 < NR ? zl[r + 1 < NR ? r + 1 : 0][v].here() : hv[H][v];
+                    const R up1 = RECON == 0 ? R(0)
+                                  : r + 2 < NR ? zl[r + 2 < NR ? r + 2 : 0][v].here() : hv[H + (r + 2 - NR < H ? r + 2 - NR : 0)][v];
+                    cell_states<RECON, R>(zl[r][v].here(), up0, up1, lo[v], hn[v]);
+                }
+                face_flux<1, GAS>(cs, hy, lo, fn);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    acc[v] = fma_r(acc[v], idx[0], (fn[v] - fy[v]) * idx[1]);
+                    fy[v] = fn[v];
+                    hy[v] = hn[v];
+                }
+            }
+            {
+                R zw[4], L[4], Rr[4], fh[4];
+                prim_of(zraw[r], zw);
+                if (more)
+                    load_raw((unsigned int)wrap_any(k + 2 + Z::AHEAD, g.nz) * plane + rowoff(r) + col, zraw[r]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) zl[r][v].push(zw[v], L[v], Rr[v]);
+                face_flux<2, GAS>(cs, L, Rr, fh);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    acc[v] = fma_r(fh[v] - fzlo[r][v], idx[2], acc[v]);
+                    fzlo[r][v] = fh[v];
+                }
+            }
+            if (live && y0 + r < g.ny) {
+                // the step's input u passes the dust floor reset (a species below its floor
+                // becomes the floor at rest) where it enters the combination, in both stages
+                R* uin = STAGE == 1 ? own : ub;
+                if (!GAS && uin[0] < dust_floor) {
+                    uin[0] = dust_floor;
+                    uin[1] = uin[2] = uin[3] = R(0);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    R L = -acc[v];
+                    // the gas acceleration acts on the raw gas density
+                    if (GAS && v > 0) L = fma_r(own[0], gx3[v - 1], L);
+                    R X;
+                    if constexpr (STAGE == 1)
+                        X = fma_r(hr, L, own[v]);
+                    else
+                        X = fma_r(hr, L, fma_r(cur_, ub[v], c1r * own[v]));
+                    st(o[v], c, X);
+                }
             }
         }
-        if (live) {
-            // the step's input u passes the dust floor reset (a species below its floor
-            // becomes the floor at rest) where it enters the combination, in both stages
-            R* uin = STAGE == 1 ? own : ub;
-            if (!gas && uin[0] < dust_floor) {
-                uin[0] = dust_floor;
-                uin[1] = uin[2] = uin[3] = R(0);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                R L = -acc[v];
-                // the gas acceleration acts on the raw gas density
-                if (gas && v > 0) L += own[0] * gx3[v - 1];
-                R X;
-                if constexpr (STAGE == 1)
-                    X = own[v] + hr * L;
-                else
-                    X = (cur_ * ub[v] + c1r * own[v]) + hr * L;
-                st(o[v], c, X);
-            }
-        }
-        if (more) store_plane(cur ^ 1);
-        __syncthreads();
     }
+}
+
+template <int RECON, int STAGE, class R, int NR>
+__global__ __launch_bounds__(64 * DWAVES) __attribute__((amdgpu_waves_per_eu(2))) void k_fluid_pass(
+    Geo g, DustParams p, PassArgs<R> a, int kz, unsigned int ntx, unsigned int nty, unsigned int ntiles,
+    unsigned int nitems, unsigned int nblk)
+{
+    __shared__ PassLds<RECON, R, NR> lds[DWAVES];
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const unsigned int item = xcd_item(blockIdx.x, nblk) * DWAVES + (unsigned int)wv;
+    if (item >= nitems) return;  // (the waves of a workgroup share nothing)
+    const int s = __builtin_amdgcn_readfirstlane((int)(item / ntiles));  // fluid: 0 gas, 1.. dust
+    const unsigned int t = item - (unsigned int)s * ntiles;
+    const int y0 = __builtin_amdgcn_readfirstlane((int)(t % nty) * NR);
+    const int x0 = __builtin_amdgcn_readfirstlane((int)((t / nty) % ntx) * DTX);
+    const int k0 = __builtin_amdgcn_readfirstlane((int)(t / (ntx * nty)) * kz);
+    const int k1 = min(k0 + kz, g.nz);
+    if (s == 0)
+        fluid_tile<RECON, STAGE, R, NR, true>(g, p, a, s, x0, y0, k0, k1, lds[wv]);
+    else
+        fluid_tile<RECON, STAGE, R, NR, false>(g, p, a, s, x0, y0, k0, k1, lds[wv]);
 }
 
 // ----------------------------------------------------------------------------------
@@ -524,34 +622,54 @@ static hipError_t drag_dispatch(const Geo& g, const DustParams& p, const DragCoe
 
 // ----------------------------------------------------------------------------------
 
+// Rows per wave and planes per chunk.  Two rows share their y faces and halo rows, and a
+// chunk primes its z pipeline once, but a small grid needs the waves: two rows where
+// chunks of four planes still give 4096 waves (two rounds of what the GPU holds at two per
+// SIMD), else one row and chunks down to two planes; beyond that about 16384 waves, whose
+// last round costs little.  FP64 stage 1, us, one row and 2 planes / two rows and 4
+// planes at least: 24^3 with 2 species 13 / 25, 40^3 with 4 29 / 28, 64^3 with 8 89 / 80,
+// 128^3 with 8 553 / 531; 192^3 with 8 by waves 8192 / 16384 / 32768: 1722 / 1670 / 1700.
 DustGrid dust_grid(const Geo& g, int nfluids)
 {
     DustGrid d;
     d.ntx = (unsigned int)((g.nx + DTX - 1) / DTX);
-    d.nty = (unsigned int)((g.ny + DTY - 1) / DTY);
-    const long long tiles = (long long)d.ntx * d.nty * nfluids;
-    // about 4096 workgroups, at least 8 planes each (the z window is primed per chunk)
-    const long long want = (4096 + tiles - 1) / tiles;
+    const long long cols = (long long)d.ntx * nfluids;
+    d.rows = cols * ((g.ny + 1) / 2) * ((g.nz + 3) / 4) >= 4096 ? 2 : 1;
+    d.nty = (unsigned int)((g.ny + d.rows - 1) / d.rows);
+    const long long tiles = cols * d.nty;
+    const long long want = (16384 + tiles - 1) / tiles;
     int kz = (int)((g.nz + want - 1) / want);
-    if (kz < 8) kz = 8;
+    const int least = d.rows == 2 ? 4 : 2;
+    if (kz < least) kz = least;
     if (kz > g.nz) kz = g.nz;
     d.kz = kz;
     d.ntz = (unsigned int)((g.nz + kz - 1) / kz);
     d.ntiles = d.ntx * d.nty * d.ntz;
-    d.nblk = d.ntiles * (unsigned int)nfluids;
+    d.nitems = d.ntiles * (unsigned int)nfluids;
+    d.nblk = (d.nitems + DWAVES - 1) / DWAVES;
     return d;
+}
+
+template <int RECON, class R, int NR>
+static hipError_t pass_rows(const Geo& g, const DustParams& p, const DustGrid& d, int stage, const PassArgs<R>& a,
+                            hipStream_t s)
+{
+    const dim3 gr(d.nblk), bl(64 * DWAVES);
+    if (stage == 1)
+        hipLaunchKernelGGL((k_fluid_pass<RECON, 1, R, NR>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles,
+                           d.nitems, d.nblk);
+    else
+        hipLaunchKernelGGL((k_fluid_pass<RECON, 2, R, NR>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles,
+                           d.nitems, d.nblk);
+    return hipGetLastError();
 }
 
 template <int RECON, class R>
 static hipError_t pass(const Geo& g, const DustParams& p, const DustGrid& d, int stage, const PassArgs<R>& a,
                        hipStream_t s)
 {
-    const dim3 gr(d.nblk), bl(DTX * DTY);
-    if (stage == 1)
-        hipLaunchKernelGGL((k_fluid_pass<RECON, 1, R>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles, d.nblk);
-    else
-        hipLaunchKernelGGL((k_fluid_pass<RECON, 2, R>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles, d.nblk);
-    return hipGetLastError();
+    if (d.rows == 2) return pass_rows<RECON, R, 2>(g, p, d, stage, a, s);
+    return pass_rows<RECON, R, 1>(g, p, d, stage, a, s);
 }
 
 template <class R>

@@ -115,10 +115,10 @@ hipError_t launch_diag(const Geo& g, int mhd, int ndust, const double* U, double
                        double* out, hipStream_t s);
 
 // ---- isothermal gas + dust (IMEX2P) ----
-// Tiling of the fluid passes: one workgroup per (fluid, 64 x 8 tile, chunk of kz planes).
+// Tiling of the fluid passes: one wave per (fluid, 64 x rows tile, chunk of kz planes).
 struct DustGrid {
-    int kz;
-    unsigned int ntx, nty, ntz, ntiles, nblk;
+    int kz, rows;
+    unsigned int ntx, nty, ntz, ntiles, nitems, nblk;
 };
 DustGrid dust_grid(const Geo& g, int nfluids);
 // Explicit parts: stage 1 writes X = u + lam dt L(u) into U1; stage 2 writes
