@@ -220,7 +220,7 @@ Layout layout(const mhd_grid* g, const mhd_physics* p, const mhd_scheme* sc)
         L.F = fp32 ? align256(field * nv) : 0;
     L.Rc = is_mhd ? align256(edge_area_bytes(n, fp32)) : 0;
     size_t nb = blocks_for(n);
-    const size_t nf = fused_grid(make_geo(g), choose_kz(g)).nblk;
+    const size_t nf = fused_grid(make_geo(g), choose_kz(g), false).nblk;
     if (nf > nb) nb = nf;
     L.partial = align256(nb * sizeof(double) * (size_t)diag_count(MHD_MAX_DUST));
     L.scalars = align256(sizeof(double) * 64);
@@ -430,9 +430,9 @@ mhd_status mhd_create(const mhd_grid* grid, const mhd_physics* phys, const mhd_s
     c->n = (long long)grid->nx * grid->ny * grid->nz;
 
     c->geo = make_geo(grid);
-    c->fg = fused_grid(c->geo, choose_kz(grid));
-    c->dg = dust_grid(c->geo, 1 + (phys->eos == MHD_EOS_ADIABATIC_MHD ? 0 : phys->ndust));
     c->fp32 = scheme->prec == MHD_PREC_FP32_BULK;
+    c->fg = fused_grid(c->geo, choose_kz(grid), c->fp32);
+    c->dg = dust_grid(c->geo, 1 + (phys->eos == MHD_EOS_ADIABATIC_MHD ? 0 : phys->ndust));
     c->cfl_scale = make_params(phys, scheme, &c->mp, &c->dp);
 
     char* base = (char*)device_workspace;

@@ -26,9 +26,10 @@ struct FusedGrid {
     int kz;                       // z planes per workgroup (both kernels)
     unsigned int ntx, nty, ntz;   // tiles of the flux/update kernel along x, y, z
     unsigned int nblk;            // workgroups of the flux/update kernel
+    bool wide;                    // its FP32 form with wide tiles
     unsigned int ctx, cty4, cty8; // tiles of the CT kernel along x, and along y for 4 / 8 rows
 };
-FusedGrid fused_grid(const Geo& g, int kz);
+FusedGrid fused_grid(const Geo& g, int kz, bool fp32);
 int flux_tile_cells();  // cells per z plane of a flux/update tile
 
 // A state register of the MHD path by role.  FP64 form (R = double): the 8 canonical

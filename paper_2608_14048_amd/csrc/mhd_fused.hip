@@ -5,6 +5,7 @@
 //                         of z planes; Riemann solves on every face of the tile, the
 //                         cell fields of the stage output (rho, M, E), and the 6 face
 //                         fields, 3 cell-E fields and flow codes the edge EMFs need.
+//                         k_flux3_wide is the FP32 kernel on TXW x TYW tiles (fused_grid).
 // k_ct_update<CFL, IN>    64-lane tiles of 8 rows (one halo row per 8); edge EMFs, the
 //                         face-field update and, in the last stage, the CFL partials.
 //                         The FP64 kernel that also reduces the time step uses 4 rows: it
@@ -20,6 +21,9 @@ using namespace tiles;
 namespace {
 constexpr int TXF = 16;  // lanes along x (flux/update kernel)
 constexpr int TYF = 16;  // rows (flux/update kernel)
+constexpr int TXW = 32;  // lanes along x (wide FP32 flux/update kernel)
+constexpr int TYW = 8;   // rows (wide FP32 flux/update kernel)
+static_assert(TXW * TYW == TXF * TYF, "both shapes cover as many cells");
 constexpr int TX = 64;   // lanes along x (CT kernel)
 constexpr int TY = 4;    // rows (FP64 CT kernel that reduces the time step)
 constexpr int TY2 = 8;   // rows (other CT kernels)
@@ -34,6 +38,20 @@ void k_flux3(Geo g, MhdParams P, StageArgs<R> a, int kz, unsigned int ntx, unsig
     const unsigned int t = xcd_tile(blockIdx.x, nblk);
     const int x0 = (int)(t % ntx) * TXF;
     const int y0 = (int)((t / ntx) % nty) * TYF;
+    const int k0 = (int)(t / (ntx * nty)) * kz;
+    Tile::run(g, P, a, x0, y0, k0, min(k0 + kz, g.nz), lds);
+}
+
+template <int RECON, int RS, bool IN>
+__global__ __launch_bounds__(TXW* TYW) __attribute__((amdgpu_waves_per_eu(FluxWaves<RECON, RS, float>::min)))
+void k_flux3_wide(Geo g, MhdParams P, StageArgs<float> a, int kz, unsigned int ntx, unsigned int nty,
+                  unsigned int nblk)
+{
+    using Tile = FluxTile<RECON, RS, IN, float, TXW, TYW>;
+    __shared__ typename Tile::Lds lds;
+    const unsigned int t = xcd_tile(blockIdx.x, nblk);
+    const int x0 = (int)(t % ntx) * TXW;
+    const int y0 = (int)((t / ntx) % nty) * TYW;
     const int k0 = (int)(t / (ntx * nty)) * kz;
     Tile::run(g, P, a, x0, y0, k0, min(k0 + kz, g.nz), lds);
 }
@@ -102,12 +120,26 @@ __global__ __launch_bounds__(kBlock) void k_unpack_fp32(long long n, RegView<flo
 // launchers
 // ----------------------------------------------------------------------------------
 
-FusedGrid fused_grid(const Geo& g, int kz)
+// FP32 takes the wide tiles wherever they are no more than the square ones: a row of the
+// tile is then a whole 128-byte line, and its x halo costs two lines for 32 cells instead
+// of two for 16 (PPM + HLLD VL2 256^3: predictor 733 -> 650 us, corrector 1210 -> 1144;
+// PLM + HLLE RK2 512 x 512 x 256, HBM-bound: 3381 -> 2787 and 3793 -> 2947 us).  Where
+// they are more, the empty lanes cost more than the lines save (101 x 75 x 54, 40 tiles a
+// plane against 35: 36.2 -> 42.3 us).  FP64 rows of 16 are whole lines already, and the
+// wide tiles' extra y halo costs its issue-bound kernels 6 % (corrector 2400 -> 2554 us).
+FusedGrid fused_grid(const Geo& g, int kz, bool fp32)
 {
     FusedGrid fg;
     fg.kz = kz;
-    fg.ntx = (unsigned int)((g.nx + TXF - 1) / TXF);
-    fg.nty = (unsigned int)((g.ny + TYF - 1) / TYF);
+    const auto tiles = [](int n, int t) { return (unsigned int)((n + t - 1) / t); };
+    fg.ntx = tiles(g.nx, TXF);
+    fg.nty = tiles(g.ny, TYF);
+    const unsigned int wx = tiles(g.nx, TXW), wy = tiles(g.ny, TYW);
+    fg.wide = fp32 && wx * wy <= fg.ntx * fg.nty;
+    if (fg.wide) {
+        fg.ntx = wx;
+        fg.nty = wy;
+    }
     fg.ntz = (unsigned int)((g.nz + kz - 1) / kz);
     fg.nblk = fg.ntx * fg.nty * fg.ntz;
     fg.ctx = (unsigned int)((g.nx + TX - 1) / TX);
@@ -122,6 +154,13 @@ template <int RECON, int RS, bool IN, class R>
 static hipError_t flux3(const Geo& g, const MhdParams& p, const FusedGrid& fg, const StageArgs<R>& a,
                         hipStream_t s)
 {
+    if constexpr (sizeof(R) == 4) {
+        if (fg.wide) {
+            hipLaunchKernelGGL((k_flux3_wide<RECON, RS, IN>), dim3(fg.nblk), dim3(TXW * TYW), 0, s, g, p, a, fg.kz,
+                               fg.ntx, fg.nty, fg.nblk);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((k_flux3<RECON, RS, IN, R>), dim3(fg.nblk), dim3(TXF * TYF), 0, s, g, p, a, fg.kz,
                        fg.ntx, fg.nty, fg.nblk);
     return hipGetLastError();
