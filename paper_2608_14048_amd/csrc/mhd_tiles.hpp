@@ -351,9 +351,12 @@ struct FluxTile {
     static constexpr int NT = TX * TY, NR = TX + TY, NW = NT / 64;
     static_assert(NT % 64 == 0 && (NW & (NW - 1)) == 0, "whole wavefronts, a power of two of them");
     static_assert(NR <= NT, "the tile's high faces need TX + TY threads");
-    // FP64 PPM: keep the compiler from hoisting the stencil loads of every variable
-    // ahead of the reconstructions (it would hold them all in registers at once)
+    // PPM: keep the compiler from hoisting the stencil loads of every variable ahead of the
+    // reconstructions (it would hold them all in registers at once), and from sinking the
+    // branch-free limiters into the branch that solves the face (their inputs would stay
+    // live in place of their results: FP64 184 bytes of scratch per lane against 12)
     static constexpr bool kFence = RECON == 2;
+    __device__ static void pin(R& u, R& v) { asm volatile("" : "+v"(u), "+v"(v)); }
     // FP64 PPM: the z pipeline reloads plane k + 1 instead of carrying it, and the x/y
     // part of a cell's flux divergence is read from LDS when the cell is completed (one
     // more barrier per plane) instead of being carried to the next pass: 24 fewer
@@ -397,7 +400,10 @@ struct FluxTile {
     #pragma unroll
             for (int s = -SL; s <= SR; ++s) st[3 + s] = at(comp[v], s);
             face_states<RECON>(st, *lr[v][0], *lr[v][1]);
-            if constexpr (kFence) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kFence) {
+                pin(*lr[v][0], *lr[v][1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 
@@ -512,6 +518,11 @@ struct FluxTile {
                         zpv.push(ak, a1, a2, l, r);
                     else
                         zpv.push(ak, a2, l, r);
+                    if constexpr (kFence) {
+                        pin(r, zpv.apl);
+                        pin(zpv.ilo, zpv.m0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 };
                 push(zp[0], wk.d, wz1.d, wz.d, L.d, Rt.d);
                 push(zp[1], wk.vz, wz1.vz, wz.vz, L.vn, Rt.vn);
@@ -681,7 +692,10 @@ struct FluxTile {
                     const int stride = ry ? LX : 1;
                     const R* swf = &sw[0][0][0];
                     recon7(comp, [&](int v, int s) { return swf[v * (LY * LX) + base + s * stride]; }, L, Rt);
-                    solve<RS>(L, Rt, ldT(ry ? a.in.b[1] : a.in.b[0], cr), P, f);
+                    // (the offset and not the pointer picked per lane: a table of the two
+                    // pointers would live in scratch memory)
+                    const long long by = a.in.b[1] - a.in.b[0];
+                    solve<RS>(L, Rt, ldT(a.in.b[0] + (ry ? by : 0), cr), P, f);
                     if (ry) {
                         lds.hy[0][TY][rq] = f.d; lds.hy[1][TY][rq] = f.mt2; lds.hy[2][TY][rq] = f.mn;
                         lds.hy[3][TY][rq] = f.mt1; lds.hy[4][TY][rq] = f.e;
@@ -719,7 +733,7 @@ struct FluxTile {
 // The FP64 PPM kernels reach three (168 registers) only in their reload form (see
 // FluxTile::kLean): the carried form held to three spilled about 36 dwords per lane and
 // ran 20 % slower (3.48 against 2.91 ms per corrector launch at 256^3), the reload form
-// spills six loop-invariant dwords and runs 2.51 against 2.67 ms.
+// ran 2.51 against 2.67 ms (with branch-free limiters 2.08, three dwords spilled).
 template <int RECON, int RS, class R>
 struct FluxWaves {
     static constexpr int min = sizeof(R) == 4 ? 4 : (RS == 1 && RECON == 1 ? 2 : 3);

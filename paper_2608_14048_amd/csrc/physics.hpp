@@ -110,50 +110,65 @@ __device__ __forceinline__ R slope_vl(R am, R a0, R ap)
     }
 }
 
-// Colella-Woodward limited central slope of the middle cell.
+// Half of Colella and Woodward's limited central slope of the middle cell: the value of
+// least magnitude of (ap - am)/4, ap - a0 and a0 - am, or 0 unless the last two share a
+// sign (the quarter is exact).  Minima, maxima and medians only: ten FP64 or six FP32
+// instructions, against twelve with a product's sign, a select and a copied sign.
 template <class R>
 __device__ __forceinline__ R cw_slope(R am, R a0, R ap)
 {
 #pragma clang fp contract(off)
-    const R dm = a0 - am, dp = ap - a0;
-    const R c = R(0.5) * (ap - am);
-    // dm and dp share a sign where the slope is kept, so c carries it; the doubling is
-    // exact, so 2 min(|dm|, |dp|) = min(2|dm|, 2|dp|) bit for bit
-    const R lim = min_r(abs_r(c), R(2) * min_r(abs_r(dm), abs_r(dp)));
-    return dm * dp > R(0) ? copysign_r(lim, c) : R(0);
+    const R dm = a0 - am, dp = ap - a0, c = R(0.25) * (ap - am);
+    if constexpr (sizeof(R) == 4) {
+        return __builtin_amdgcn_fmed3f(c, __builtin_amdgcn_fmed3f(dm, dp, 0.0f), 0.0f);
+    } else {
+        const R up = max_r(min_r(dm, dp), R(0)), dn = min_r(max_r(dm, dp), R(0));
+        return max_r(min_r(c, up), dn);
+    }
 }
 
-// Colella-Woodward interface value between cells a0 and a1 from their limited slopes
-// (the fourth-order average, monotonised through the slopes):
-// a0 + (a1 - a0)/2 - (m1 - m0)/6.
+// Colella-Woodward interface value between cells a0 and a1 from the halves m0, m1 of
+// their limited slopes (the fourth-order average, monotonised through the slopes):
+// a0 + (a1 - a0)/2 - 2 (m1 - m0)/6.
 template <class R>
 __device__ __forceinline__ R cw_interface(R a0, R a1, R m0, R m1)
 {
 #pragma clang fp contract(off)
     const R t = fma_r(R(0.5), a1 - a0, a0);
-    return fma_r(m0 - m1, R(1.0 / 6.0), t);
+    return fma_r(m0 - m1, R(2) * R(1.0 / 6.0), t);
 }
 
-// Colella-Woodward monotonisation of a parabola (centre a, edges lo, hi).  Divergent on
-// purpose: few lanes steepen, whole waves skip it, and as selects the extra live edges
-// spill (FP64 corrector 2.4 -> 3.9 ms, FP32 1.25 -> 1.59 ms at 256^3).
-template <class R>
-__device__ __forceinline__ void cw_limit(R a, R& lo, R& hi)
+// One edge of a parabola with centre a monotonised against its other edge: the median of
+// a, the edge and 3a - 2 other, which is Colella and Woodward's choice (a at an extremum,
+// 3a - 2 other where the parabola overshoots, else the edge unchanged).
+__device__ __forceinline__ double cw_edge(double a, double edge, double other)
+{
+    const double x = fma_r(-2.0, other, 3.0 * a);
+    return max_r(min_r(edge, x), min_r(max_r(edge, x), a));
+}
+
+// Colella-Woodward monotonisation of a parabola (centre a, edges lo, hi), without a
+// branch (against branches on the conditions, 256^3 VL2 + HLLD corrector, with the slopes
+// above: FP64 2357 -> 2078 us, FP32 1142 -> 1034; a caller that needs one edge costs one).
+// FP64: medians.  FP32: the conditions as written, whose rounding decides which edge moves.
+__device__ __forceinline__ void cw_limit(double a, double& lo, double& hi)
+{
+    const double l = cw_edge(a, lo, hi);
+    hi = cw_edge(a, hi, lo);
+    lo = l;
+}
+__device__ __forceinline__ void cw_limit(float a, float& lo, float& hi)
 {
 #pragma clang fp contract(off)
-    if ((hi - a) * (a - lo) <= R(0)) {
-        lo = a;
-        hi = a;
-        return;
-    }
-    const R da = hi - lo;
-    const R a6 = R(6) * fma_r(R(-0.5), lo + hi, a);
-    const R da2 = da * da;
-    const R p = da * a6;
-    if (p > da2)
-        lo = fma_r(R(-2), hi, R(3) * a);
-    else if (-da2 > p)
-        hi = fma_r(R(-2), lo, R(3) * a);
+    const bool flat = (hi - a) * (a - lo) <= 0.0f;
+    const float da = hi - lo;
+    const float a6 = 6.0f * fma_r(-0.5f, lo + hi, a);
+    const float da2 = da * da;
+    const float p = da * a6;
+    const float l = p > da2 ? fma_r(-2.0f, hi, 3.0f * a) : lo;
+    const float h = -da2 > p ? fma_r(-2.0f, lo, 3.0f * a) : hi;
+    lo = flat ? a : l;
+    hi = flat ? a : h;
 }
 
 template <int RECON, class R>
