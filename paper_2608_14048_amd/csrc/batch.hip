@@ -49,11 +49,6 @@ constexpr int kFluxTX[kShapes] = {64, 32, 16};
 constexpr int kCtTX[kShapes] = {64, 32, 16};
 constexpr int kAlignCells = 64;  // block offsets in cells: keeps every field 256-B aligned
 
-struct BlockDesc {
-    Geo g;
-    unsigned long long off;  // first cell of the block in the batch
-};
-
 struct WorkItem {
     int block, x0, y0, k0, k1, shape;
 };
@@ -670,16 +665,20 @@ mhd_status bstep(mhd_batch* c)
     }
 }
 
-// The canonical FP64 state of block b on the device (the register itself, or unpacked
-// into the staging area).
-const double* bcanon(mhd_batch* c, int b, hipError_t* e)
+// Workgroups of a block in the launches that load and store all states: about 8192 in all,
+// and never more CFL partials than a partial per 256 cells (the area holds at least those
+// and one per block).
+int state_grid(const mhd_batch* c)
 {
-    *e = hipSuccess;
-    char* r = c->reg[c->cur] + c->off[b] * (unsigned long long)c->reg_bpc;
-    if (!c->fp32) return (const double*)r;
-    double* st = (double*)c->F + c->off[b] * 8ULL;
-    *e = launch_unpack_fp32(c->geo[b], r, st, c->stream);
-    return st;
+    const long long cap = (long long)blocks_for((long long)c->ncell) / c->nb;
+    return (int)std::max(1LL, std::min((8191LL + c->nb) / c->nb, cap));
+}
+
+size_t state_bytes(const mhd_batch* c)
+{
+    size_t t = 0;
+    for (const Geo& g : c->geo) t += (size_t)g.n * 8 * sizeof(double);
+    return t;
 }
 
 }  // namespace
@@ -727,6 +726,7 @@ mhd_status mhd_batch_create(int nblocks, const mhd_grid* grids, const mhd_physic
     c->cap_f = L.cap_f;
     c->cap_c = L.cap_c;
     std::vector<BlockDesc> desc(nblocks);
+    unsigned long long at = 0;
     for (int b = 0; b < nblocks; ++b) {
         const mhd_grid& g = grids[b];
         Geo q;
@@ -738,7 +738,8 @@ mhd_status mhd_batch_create(int nblocks, const mhd_grid* grids, const mhd_physic
             q.inv_dx[a] = 1.0 / q.dx[a];
         }
         c->geo.push_back(q);
-        desc[b] = BlockDesc{q, L.off[b]};
+        desc[b] = BlockDesc{q, L.off[b], at};
+        at += (unsigned long long)q.n;
         c->shape.push_back(default_shape(g.nx));
     }
     int dev = 0;
@@ -786,9 +787,7 @@ mhd_status mhd_batch_create(int nblocks, const mhd_grid* grids, const mhd_physic
 mhd_status mhd_batch_state_len(const mhd_batch* c, size_t* n)
 {
     if (!c || !n) return MHD_E_INVAL;
-    size_t t = 0;
-    for (const Geo& g : c->geo) t += (size_t)g.n * 8;
-    *n = t;
+    *n = state_bytes(c) / sizeof(double);
     return MHD_OK;
 }
 
@@ -796,22 +795,18 @@ mhd_status mhd_batch_set_state(mhd_batch* c, const double* src, int src_is_devic
 {
     if (!c || !src) return MHD_E_INVAL;
     hipError_t e = hipSuccess;
-    size_t at = 0;
-    for (int b = 0; b < c->nb && e == hipSuccess; ++b) {
-        const size_t nbytes = (size_t)c->geo[b].n * 8 * sizeof(double);
-        char* dst = c->fp32 ? (char*)c->F + c->off[b] * 64ULL : c->reg[c->cur] + c->off[b] * (unsigned long long)c->reg_bpc;
-        e = hipMemcpyAsync(dst, src + at, nbytes, src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+    const double* d = src;
+    // host memory (and device memory off a double's alignment) by way of the face area,
+    // which holds at least 8 doubles per cell
+    if (!src_is_device || ((uintptr_t)src & 7u)) {
+        e = hipMemcpyAsync(c->F, src, state_bytes(c), src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                            c->stream);
-        at += (size_t)c->geo[b].n * 8;
+        d = (const double*)c->F;
     }
+    if (e == hipSuccess)
+        e = launch_batch_load(c->d_blk, c->nb, state_grid(c), c->mp, c->fp32, d, c->reg[c->cur], c->partial, c->dt,
+                              c->cfl_scale, c->stream);
     if (e == hipSuccess && !src_is_device) e = hipStreamSynchronize(c->stream);
-    for (int b = 0; b < c->nb && e == hipSuccess; ++b) {
-        const double* canon = c->fp32 ? (const double*)((char*)c->F + c->off[b] * 64ULL)
-                                      : (const double*)(c->reg[c->cur] + c->off[b] * (unsigned long long)c->reg_bpc);
-        e = launch_cfl_mhd(c->geo[b], c->mp, canon, c->partial, c->dt + b, c->cfl_scale, c->stream);
-        if (e == hipSuccess && c->fp32)
-            e = launch_pack_fp32(c->geo[b], canon, c->reg[c->cur] + c->off[b] * (unsigned long long)c->reg_bpc, c->stream);
-    }
     if (e == hipSuccess && c->coupled) return domain_after_stage(c, c->reg[c->cur], true);
     return bdev(e);
 }
@@ -819,16 +814,12 @@ mhd_status mhd_batch_set_state(mhd_batch* c, const double* src, int src_is_devic
 mhd_status mhd_batch_get_state(mhd_batch* c, double* dst, int dst_is_device)
 {
     if (!c || !dst) return MHD_E_INVAL;
-    hipError_t e = hipSuccess;
-    size_t at = 0;
-    for (int b = 0; b < c->nb && e == hipSuccess; ++b) {
-        const double* canon = bcanon(c, b, &e);
-        if (e != hipSuccess) break;
-        const size_t nbytes = (size_t)c->geo[b].n * 8 * sizeof(double);
-        e = hipMemcpyAsync(dst + at, canon, nbytes, dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+    const bool direct = dst_is_device && !((uintptr_t)dst & 7u);
+    double* d = direct ? dst : (double*)c->F;
+    hipError_t e = launch_batch_store(c->d_blk, c->nb, state_grid(c), c->fp32, c->reg[c->cur], d, c->stream);
+    if (e == hipSuccess && !direct)
+        e = hipMemcpyAsync(dst, d, state_bytes(c), dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
                            c->stream);
-        at += (size_t)c->geo[b].n * 8;
-    }
     if (e == hipSuccess && !dst_is_device) e = hipStreamSynchronize(c->stream);
     return bdev(e);
 }
@@ -999,7 +990,7 @@ mhd_status mhd_batch_couple(mhd_batch* c, const int nblocks_xyz[3], int ghost, c
             c->geo[b].dx[a] = length[a] / m.dn[a];
             c->geo[b].inv_dx[a] = 1.0 / c->geo[b].dx[a];
         }
-        desc[b] = BlockDesc{c->geo[b], c->off[b]};
+        desc[b] = BlockDesc{c->geo[b], c->off[b], (unsigned long long)b * (unsigned long long)m.pc};
     }
     hipError_t e = hipMemcpyAsync(c->d_blk, desc.data(), desc.size() * sizeof(BlockDesc), hipMemcpyHostToDevice,
                                   c->stream);

@@ -61,7 +61,7 @@ __host__ __device__ inline RegView<R> reg_view(void* base, long long n)
     }
     return v;
 }
-inline size_t register_bytes(long long n, bool fp32)
+__host__ __device__ inline size_t register_bytes(long long n, bool fp32)
 {
     return fp32 ? (size_t)n * (sizeof(double) + 7 * sizeof(float)) : (size_t)n * 8 * sizeof(double);
 }
@@ -105,6 +105,19 @@ hipError_t launch_cfl_mhd(const Geo& g, const MhdParams& p, const double* U, dou
 hipError_t launch_cfl_blocks(const Geo& pg, const MhdParams& p, const double* reg, const unsigned long long* off,
                              int nb, int ghost, int bx, int by, int bz, double* partial, double* dt_out,
                              double scale, hipStream_t s);
+// A block of a batch: its grid, and its first cell in the registers (offsets padded) and
+// in a state of all blocks one after the other.
+struct BlockDesc {
+    Geo g;
+    unsigned long long off, at;
+};
+// The states of all nb blocks, canonical FP64 one after the other, into the registers
+// (FP32-bulk: rounded), with every block's CFL step times scale into dt[]; per: workgroups
+// of a block, partial: nb * per doubles.  And back.
+hipError_t launch_batch_load(const BlockDesc* blk, int nb, int per, const MhdParams& p, bool fp32, const double* src,
+                             void* reg, double* partial, double* dt, double scale, hipStream_t s);
+hipError_t launch_batch_store(const BlockDesc* blk, int nb, int per, bool fp32, const void* reg, double* dst,
+                              hipStream_t s);
 hipError_t launch_cfl_dust(const Geo& g, const DustParams& p, const double* U,
                            double* partial, double* dt_out, double scale, hipStream_t s);
 // out[0] = scale * (NaN-propagating) min of partial[0..m)

@@ -1,0 +1,54 @@
+"""States of uneven batches in and out: every block's time step and fields bit for bit
+those of the same block in a context of its own, from host and device memory (also off a
+double's alignment), in both precisions; blocks smaller than a wavefront, of padded and
+unpadded cell counts, fewer and more blocks than workgroups would be launched for one.
+"""
+import numpy as np
+import pytest
+
+from paper_2608_14048_amd import binding as B
+from tests.test_gpu_parity import random_mhd
+
+pytestmark = pytest.mark.gpu
+
+SETS = {"one": [(40, 24, 33)], "tiny": [(1, 1, 2), (3, 1, 1), (5, 7, 2)] * 3,
+        "uneven": [(16, 16, 16), (33, 9, 20), (64, 48, 10), (2, 2, 2)], "many": [(4, 5, 3), (8, 4, 2)] * 150}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_bulk"])
+@pytest.mark.parametrize("name", list(SETS))
+def test_batch_state_round_trip(name, prec):
+    import torch
+
+    shapes = SETS[name]
+    scheme = dict(recon="dc", riemann="hlle", integ="vl2", prec=prec)
+    states = [random_mhd(sh, b % 7) for b, sh in enumerate(shapes)]
+    lengths = [tuple(v / max(sh) for v in sh) for sh in shapes]
+    dts, rows, alone = [], [], {}
+    for b, (sh, L) in enumerate(zip(shapes, lengths)):
+        if (sh, b % 7) not in alone:
+            sim = B.Sim(sh, L, scheme=scheme)
+            sim.set_state(states[b])
+            alone[sh, b % 7] = sim.dt_cfl(), sim.state()
+            sim.close()
+        dts.append(alone[sh, b % 7][0])
+        rows.append(alone[sh, b % 7][1])
+    dts, ref, flat = np.array(dts), np.concatenate(rows), np.concatenate(states)
+    bt = B.Batch(shapes, lengths, scheme=scheme)
+    try:
+        shifted = torch.zeros(flat.nbytes + 8, dtype=torch.uint8, device="cuda:0")
+        shifted[4:-4] = torch.from_numpy(flat).view(torch.uint8).to("cuda:0")
+        back = torch.zeros_like(shifted)
+        dev = torch.from_numpy(flat).to("cuda:0")
+        for put in (lambda: bt.set_state(states), lambda: bt.set_state(dev),
+                    lambda: B.mhd_batch_set_state(bt.ctx, shifted.data_ptr() + 4, True)):
+            bt.set_state(np.ones_like(flat))
+            put()
+            assert np.array_equal(bt.dt_cfl(), dts)
+            assert np.array_equal(bt.state(), ref)
+            assert np.array_equal(bt.state(device=True).cpu().numpy(), ref)
+            B.mhd_batch_get_state(bt.ctx, back.data_ptr() + 4, True)
+            torch.cuda.synchronize()
+            assert np.array_equal(back[4:-4].cpu().numpy().view(np.float64), ref)
+    finally:
+        bt.close()
