@@ -113,8 +113,8 @@ __global__ __launch_bounds__(kBlock) void k_cfl_blocks(Geo pg, MhdParams p, cons
 
 // All blocks of a batch in one launch, `per` workgroups striding over the cells of each:
 // bound by its bytes, where a copy, a reduction, its final pass and a conversion per block
-// were bound by their launches (512 blocks, 26.8 M cells, FP32-bulk: 6.9 -> 0.62 ms, and the
-// way back 4.0 -> 0.56 ms of kernels; with the gaps between them 8.4 ms of both).
+// were bound by their launches (512 blocks, 26.8 M cells, FP32-bulk: 0.62 ms in
+// and 0.56 ms back; the pair took 9.6 ms).
 template <class R>
 __global__ __launch_bounds__(kBlock) void k_batch_load(const BlockDesc* __restrict__ blk, int per, MhdParams p,
                                                        const double* __restrict__ src, char* __restrict__ reg,
