@@ -112,8 +112,9 @@ Geo make_geo(const mhd_grid* grid);
 
 // z planes per workgroup of the MHD kernels: about 3072 flux/update workgroups (four
 // rounds of the 768 that the FP64 PPM kernel keeps resident, three per CU; targets of
-// 1536, 2304 and 4608 measured no faster at 256^3), and at least two planes per chunk.  Each chunk primes its z pipeline once (five planes for PPM),
-// which small grids afford: at 64^3 chunks of 2 planes took the step from 0.355 to
+// 1536, 2304 and 4608 measured no faster at 256^3), and at least two planes per
+// chunk (one on the smallest grids).  Each chunk primes its z pipeline once (five planes
+// for PPM), which small grids afford: at 64^3 chunks of 2 planes took the step from 0.355 to
 // 0.192 ms against chunks of 8, with no change at 256^3.
 int choose_kz(const mhd_grid* g)
 {
@@ -121,7 +122,7 @@ int choose_kz(const mhd_grid* g)
     const long long tiles = ((long long)g->nx * g->ny + per_plane - 1) / per_plane;
     const long long want = (3072 + tiles - 1) / tiles;
     int kz = (int)((g->nz + want - 1) / want);
-    if (kz < 2) kz = 2;
+    if (kz < 2) kz = one_plane_flux(make_geo(g)) ? 1 : 2;
     if (kz > g->nz) kz = g->nz;
     return kz;
 }

@@ -23,13 +23,15 @@ struct DustParams {
 
 // ---- adiabatic MHD (z-marching tile kernels) ----
 struct FusedGrid {
-    int kz;                       // z planes per workgroup (both kernels)
+    int kz, ckz;                  // z planes per workgroup (flux/update, CT kernel)
     unsigned int ntx, nty, ntz;   // tiles of the flux/update kernel along x, y, z
     unsigned int nblk;            // workgroups of the flux/update kernel
     bool wide;                    // its FP32 form with wide tiles
     unsigned int ctx, cty4, cty8; // tiles of the CT kernel along x, and along y for 4 / 8 rows
+    unsigned int ctz;             // and along z
 };
 FusedGrid fused_grid(const Geo& g, int kz, bool fp32);
+bool one_plane_flux(const Geo& g);  // flux/update workgroups of a single plane each
 int flux_tile_cells();  // cells per z plane of a flux/update tile
 
 // A state register of the MHD path by role.  FP64 form (R = double): the 8 canonical

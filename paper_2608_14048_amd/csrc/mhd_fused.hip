@@ -120,6 +120,17 @@ __global__ __launch_bounds__(kBlock) void k_unpack_fp32(long long n, RegView<flo
 // launchers
 // ----------------------------------------------------------------------------------
 
+// On a grid whose planes, one workgroup each, all run at once (three workgroups of the
+// FP64 kernels per CU), a workgroup takes one plane and not two: what it takes is then its
+// own chain of loads and solves (PPM + HLLD corrector 32^3 31.4 -> 20.6 us, 96 x 96 x 16
+// 48.0 -> 40.2; 56^3, 896 workgroups: 47.5 -> 50.1).  The CT kernel alike (32^3 11.5 -> 8.9
+// and 16.5 -> 13.6 us, 64^3 15.4 -> 14.1 and 23.0 -> 21.5; 101 x 75 x 54, 1080 workgroups:
+// 23.2 -> 24.1).  The CFL partials then stay below the 28 per flux/update workgroup that
+// the workspace holds: at most 8 (4-row tiles of one plane against 16-row tiles of two).
+constexpr long long kAtOnce = 768;
+static long long tiles_of(int n, int t) { return (n + t - 1) / t; }
+bool one_plane_flux(const Geo& g) { return tiles_of(g.nx, TXF) * tiles_of(g.ny, TYF) * g.nz <= kAtOnce; }
+
 // FP32 takes the wide tiles wherever they are no more than the square ones: a row of the
 // tile is then a whole 128-byte line, and its x halo costs two lines for 32 cells instead
 // of two for 16 (PPM + HLLD VL2 256^3: predictor 733 -> 650 us, corrector 1210 -> 1144;
@@ -131,7 +142,7 @@ FusedGrid fused_grid(const Geo& g, int kz, bool fp32)
 {
     FusedGrid fg;
     fg.kz = kz;
-    const auto tiles = [](int n, int t) { return (unsigned int)((n + t - 1) / t); };
+    const auto tiles = [](int n, int t) { return (unsigned int)tiles_of(n, t); };
     fg.ntx = tiles(g.nx, TXF);
     fg.nty = tiles(g.ny, TYF);
     const unsigned int wx = tiles(g.nx, TXW), wy = tiles(g.ny, TYW);
@@ -145,6 +156,8 @@ FusedGrid fused_grid(const Geo& g, int kz, bool fp32)
     fg.ctx = (unsigned int)((g.nx + TX - 1) / TX);
     fg.cty4 = (unsigned int)((g.ny + TY - 1) / TY);
     fg.cty8 = (unsigned int)((g.ny + TY2 - 1) / TY2);
+    fg.ckz = kz <= 2 && (long long)fg.ctx * fg.cty8 * g.nz <= kAtOnce ? 1 : kz;
+    fg.ctz = tiles(g.nz, fg.ckz);
     return fg;
 }
 
@@ -206,26 +219,26 @@ static hipError_t ct_update(const Geo& g, const MhdParams& p, const FusedGrid& f
     CtArgs<R> a{reg_view<R>(in, g.n), reg_view<R>(base, g.n), (const R*)F, (const R*)Rc,
                 flow_area<R>(const_cast<void*>(Rc), g.n), reg_view<R>(out, g.n), partial, coef};
     const bool use_in = coef.g0 != 0.0;
-    const unsigned int nb8 = fg.ctx * fg.cty8 * fg.ntz;
+    const unsigned int nb8 = fg.ctx * fg.cty8 * fg.ctz;
     if (dt_out) {
         // FP64: 4-row tiles; FP32: 8 rows
         constexpr int TYC = sizeof(R) == 8 ? TY : TY2;
         const unsigned int nty = sizeof(R) == 8 ? fg.cty4 : fg.cty8;
-        const unsigned int nblk = fg.ctx * nty * fg.ntz;
+        const unsigned int nblk = fg.ctx * nty * fg.ctz;
         const dim3 grc(nblk), blc(TX * TYC);
         if (use_in)
-            hipLaunchKernelGGL((k_ct_update<true, true, R, TYC>), grc, blc, 0, s, g, p, a, fg.kz, fg.ctx, nty, nblk);
+            hipLaunchKernelGGL((k_ct_update<true, true, R, TYC>), grc, blc, 0, s, g, p, a, fg.ckz, fg.ctx, nty, nblk);
         else
-            hipLaunchKernelGGL((k_ct_update<true, false, R, TYC>), grc, blc, 0, s, g, p, a, fg.kz, fg.ctx, nty, nblk);
+            hipLaunchKernelGGL((k_ct_update<true, false, R, TYC>), grc, blc, 0, s, g, p, a, fg.ckz, fg.ctx, nty, nblk);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_min_final(partial, nblk, cfl_scale, dt_out, s);
     }
     const dim3 gr(nb8), bl(TX * TY2);
     if (use_in)
-        hipLaunchKernelGGL((k_ct_update<false, true, R, TY2>), gr, bl, 0, s, g, p, a, fg.kz, fg.ctx, fg.cty8, nb8);
+        hipLaunchKernelGGL((k_ct_update<false, true, R, TY2>), gr, bl, 0, s, g, p, a, fg.ckz, fg.ctx, fg.cty8, nb8);
     else
-        hipLaunchKernelGGL((k_ct_update<false, false, R, TY2>), gr, bl, 0, s, g, p, a, fg.kz, fg.ctx, fg.cty8, nb8);
+        hipLaunchKernelGGL((k_ct_update<false, false, R, TY2>), gr, bl, 0, s, g, p, a, fg.ckz, fg.ctx, fg.cty8, nb8);
     return hipGetLastError();
 }
 
