@@ -118,6 +118,9 @@ struct BlockDesc {
 // of a block, partial: nb * per doubles.  And back.
 hipError_t launch_batch_load(const BlockDesc* blk, int nb, int per, const MhdParams& p, bool fp32, const double* src,
                              void* reg, double* partial, double* dt, double scale, hipStream_t s);
+// The same for one grid (partial: ceil(n/kBlock) doubles).
+hipError_t launch_state_load(const Geo& g, const MhdParams& p, bool fp32, const double* src, void* reg,
+                             double* partial, double* dt, double scale, hipStream_t s);
 hipError_t launch_batch_store(const BlockDesc* blk, int nb, int per, bool fp32, const void* reg, double* dst,
                               hipStream_t s);
 hipError_t launch_cfl_dust(const Geo& g, const DustParams& p, const double* U,

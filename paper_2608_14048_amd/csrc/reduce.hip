@@ -116,16 +116,14 @@ __global__ __launch_bounds__(kBlock) void k_cfl_blocks(Geo pg, MhdParams p, cons
 // were bound by their launches (512 blocks, 26.8 M cells, FP32-bulk: 0.62 ms in
 // and 0.56 ms back; the pair took 9.6 ms).
 template <class R>
-__global__ __launch_bounds__(kBlock) void k_batch_load(const BlockDesc* __restrict__ blk, int per, MhdParams p,
-                                                       const double* __restrict__ src, char* __restrict__ reg,
-                                                       double* __restrict__ partial)
+__device__ __forceinline__ double load_block(const BlockDesc& d, const MhdParams& p, const double* __restrict__ src,
+                                             char* __restrict__ reg, int w, int per)
 {
-    const BlockDesc d = blk[blockIdx.x / per];
     const long long n = d.g.n;
     const double* U = src + 8ULL * d.at;
     const RegView<R> v = reg_view<R>(reg + d.off * (unsigned long long)register_bytes(1, sizeof(R) == 4), n);
     double r = INFINITY;
-    for (long long c = (long long)(blockIdx.x % per) * kBlock + threadIdx.x; c < n; c += (long long)per * kBlock) {
+    for (long long c = (long long)w * kBlock + threadIdx.x; c < n; c += (long long)per * kBlock) {
         int i, j, k;
         cell_ijk(d.g, c, i, j, k);
         r = min_nan(r, cfl_cell(d.g, p, U, n, c, shifted(d.g, i, j, k, 0, 1), shifted(d.g, i, j, k, 1, 1),
@@ -138,7 +136,25 @@ __global__ __launch_bounds__(kBlock) void k_batch_load(const BlockDesc* __restri
         }
         v.E[c] = U[4 * n + c];
     }
-    r = block_min(r);
+    return block_min(r);
+}
+
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_batch_load(const BlockDesc* __restrict__ blk, int per, MhdParams p,
+                                                       const double* __restrict__ src, char* __restrict__ reg,
+                                                       double* __restrict__ partial)
+{
+    const double r = load_block<R>(blk[blockIdx.x / per], p, src, reg, (int)(blockIdx.x % per), per);
+    if (threadIdx.x == 0) partial[blockIdx.x] = r;
+}
+
+// The state of one grid in one pass over it, where a copy or a conversion and the
+// reduction each read it (256^3 FP64 426 + 228 -> 424 us, FP32-bulk 227 + 269 -> 339 us).
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_state_load(Geo g, MhdParams p, const double* __restrict__ src,
+                                                       char* __restrict__ reg, double* __restrict__ partial)
+{
+    const double r = load_block<R>(BlockDesc{g, 0, 0}, p, src, reg, (int)blockIdx.x, (int)gridDim.x);
     if (threadIdx.x == 0) partial[blockIdx.x] = r;
 }
 
@@ -241,6 +257,18 @@ hipError_t launch_cfl_mhd(const Geo& g, const MhdParams& p, const double* U, dou
     const unsigned int nb = blocks_for(g.n);
     hipLaunchKernelGGL(k_cfl_mhd, dim3(nb), dim3(kBlock), 0, s, g, p, U, partial);
     hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_state_load(const Geo& g, const MhdParams& p, bool fp32, const double* src, void* reg,
+                             double* partial, double* dt, double scale, hipStream_t s)
+{
+    const unsigned int nb = std::min(blocks_for(g.n), 16384u);
+    if (fp32)
+        hipLaunchKernelGGL(k_state_load<float>, dim3(nb), dim3(kBlock), 0, s, g, p, src, (char*)reg, partial);
+    else
+        hipLaunchKernelGGL(k_state_load<double>, dim3(nb), dim3(kBlock), 0, s, g, p, src, (char*)reg, partial);
+    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt);
     return hipGetLastError();
 }
 

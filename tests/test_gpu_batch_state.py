@@ -52,3 +52,28 @@ def test_batch_state_round_trip(name, prec):
             assert np.array_equal(back[4:-4].cpu().numpy().view(np.float64), ref)
     finally:
         bt.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_bulk"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (5, 7, 2), (64, 48, 10), (256, 130, 129)])
+def test_device_state_as_host_state(shape, prec):
+    """One grid: a state from device memory (also off a double's alignment) gives the bits
+    and the time step of the same state from host memory, which goes another way (the last
+    grid has more cells than one pass of its workgroups)."""
+    import torch
+
+    st = random_mhd(shape, 2)
+    sim = B.Sim(shape, scheme=dict(recon="dc", riemann="hlle", integ="vl2", prec=prec))
+    try:
+        sim.set_state(st)
+        dt, ref = sim.dt_cfl(), sim.state()
+        shifted = torch.zeros(st.nbytes + 8, dtype=torch.uint8, device="cuda:0")
+        shifted[4:-4] = torch.from_numpy(np.ascontiguousarray(st).reshape(-1)).view(torch.uint8).to("cuda:0")
+        dev = torch.from_numpy(np.ascontiguousarray(st).reshape(-1)).to("cuda:0")
+        for put in (lambda: sim.set_state(dev), lambda: B.mhd_set_state(sim.ctx, shifted.data_ptr() + 4, True)):
+            sim.set_state(np.ones_like(st))
+            put()
+            assert sim.dt_cfl() == dt
+            assert np.array_equal(sim.state(), ref)
+    finally:
+        sim.close()
