@@ -121,6 +121,8 @@ hipError_t launch_batch_load(const BlockDesc* blk, int nb, int per, const MhdPar
 // The same for one grid (partial: ceil(n/kBlock) doubles).
 hipError_t launch_state_load(const Geo& g, const MhdParams& p, bool fp32, const double* src, void* reg,
                              double* partial, double* dt, double scale, hipStream_t s);
+hipError_t launch_dust_load(const Geo& g, const DustParams& p, bool fp32, const double* src, void* reg,
+                            double* partial, double* dt, double scale, hipStream_t s);
 hipError_t launch_batch_store(const BlockDesc* blk, int nb, int per, bool fp32, const void* reg, double* dst,
                               hipStream_t s);
 hipError_t launch_cfl_dust(const Geo& g, const DustParams& p, const double* U,

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from paper_2608_14048_amd import binding as B
+from paper_2608_14048_amd import inputs as I
 from tests.test_gpu_parity import random_mhd
 
 pytestmark = pytest.mark.gpu
@@ -70,6 +71,33 @@ def test_device_state_as_host_state(shape, prec):
         shifted = torch.zeros(st.nbytes + 8, dtype=torch.uint8, device="cuda:0")
         shifted[4:-4] = torch.from_numpy(np.ascontiguousarray(st).reshape(-1)).view(torch.uint8).to("cuda:0")
         dev = torch.from_numpy(np.ascontiguousarray(st).reshape(-1)).to("cuda:0")
+        for put in (lambda: sim.set_state(dev), lambda: B.mhd_set_state(sim.ctx, shifted.data_ptr() + 4, True)):
+            sim.set_state(np.ones_like(st))
+            put()
+            assert sim.dt_cfl() == dt
+            assert np.array_equal(sim.state(), ref)
+    finally:
+        sim.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_bulk"])
+@pytest.mark.parametrize("nd,shape", [(1, (1, 1, 1)), (3, (13, 11, 7)), (16, (65, 8, 9))])
+def test_device_dust_state_as_host_state(nd, shape, prec):
+    """The same for gas and dust, species below their floor among them."""
+    import torch
+
+    st, ts = I.dust_drift(shape=shape, nd=nd, seed=2, noise=0.3)
+    st = np.ascontiguousarray(st, dtype=np.float64).reshape(-1)
+    n = int(np.prod(shape))
+    st[4 * n] = 0.0  # one dust cell below its floor
+    sim = B.Sim(shape, physics=dict(eos="isothermal_hydro", tstop=ts),
+                scheme=dict(recon="plm", riemann="hlle", integ="imex2p", prec=prec))
+    try:
+        sim.set_state(st)
+        dt, ref = sim.dt_cfl(), sim.state()
+        shifted = torch.zeros(st.nbytes + 8, dtype=torch.uint8, device="cuda:0")
+        shifted[4:-4] = torch.from_numpy(st).view(torch.uint8).to("cuda:0")
+        dev = torch.from_numpy(st).to("cuda:0")
         for put in (lambda: sim.set_state(dev), lambda: B.mhd_set_state(sim.ctx, shifted.data_ptr() + 4, True)):
             sim.set_state(np.ones_like(st))
             put()
