@@ -58,13 +58,13 @@ STAGE_ALGO_BYTES_FP32 = {"predictor": 72.0, "corrector": 108.0}
 # stage: which stage's bytes the dominant-kernel roofline uses.
 KERNEL_ALGO = {
     # stage input (8 fields) and, corrector, the base register's cell fields (5) in;
-    # 5 cell fields, 9 face fields and 3 cell E fields out
-    "mhd_flux_update_corrector": {"bytes": (8 + 5 + 5 + 12) * 8, "flops": 1701 + 40, "stage": "corrector"},
-    "mhd_flux_update_predictor": {"bytes": (8 + 5 + 12) * 8, "flops": 1155 + 40, "stage": "predictor"},
-    # 12 face/cell fields and the base face fields (3) in, 3 face fields out; the
+    # 5 cell fields, 6 face fields, 3 cell E fields and a byte of flow codes out
+    "mhd_flux_update_corrector": {"bytes": (8 + 5 + 5 + 9) * 8 + 1, "flops": 1701 + 40, "stage": "corrector"},
+    "mhd_flux_update_predictor": {"bytes": (8 + 5 + 9) * 8 + 1, "flops": 1155 + 40, "stage": "predictor"},
+    # 9 face/cell fields, the codes and the base face fields (3) in, 3 face fields out; the
     # corrector also reads the 5 new cell fields for the time step
-    "mhd_ct_corrector": {"bytes": (12 + 3 + 3 + 5) * 8, "flops": 152, "stage": "corrector"},
-    "mhd_ct_predictor": {"bytes": (12 + 3 + 3) * 8, "flops": 80, "stage": "predictor"},
+    "mhd_ct_corrector": {"bytes": (9 + 3 + 3 + 5) * 8 + 1, "flops": 152, "stage": "corrector"},
+    "mhd_ct_predictor": {"bytes": (9 + 3 + 3) * 8 + 1, "flops": 80, "stage": "predictor"},
     "cfl": {"bytes": 8 * 8, "flops": 72},
 }
 
@@ -72,10 +72,10 @@ KERNEL_ALGO = {
 # B; face fields 12 B), a face or cell-E field 4 B; the flops are those of the FP64
 # table, in FP32 (E's update in FP64)
 KERNEL_ALGO_FP32 = {
-    "mhd_flux_update_corrector": {"bytes": 36 + 20 + 20 + 12 * 4, "flops": 1741, "stage": "corrector"},
-    "mhd_flux_update_predictor": {"bytes": 36 + 20 + 12 * 4, "flops": 1195, "stage": "predictor"},
-    "mhd_ct_corrector": {"bytes": 12 * 4 + 12 + 12 + 20, "flops": 152, "stage": "corrector"},
-    "mhd_ct_predictor": {"bytes": 12 * 4 + 12 + 12, "flops": 80, "stage": "predictor"},
+    "mhd_flux_update_corrector": {"bytes": 36 + 20 + 20 + 9 * 4 + 1, "flops": 1741, "stage": "corrector"},
+    "mhd_flux_update_predictor": {"bytes": 36 + 20 + 9 * 4 + 1, "flops": 1195, "stage": "predictor"},
+    "mhd_ct_corrector": {"bytes": 9 * 4 + 1 + 12 + 12 + 20, "flops": 152, "stage": "corrector"},
+    "mhd_ct_predictor": {"bytes": 9 * 4 + 1 + 12 + 12, "flops": 80, "stage": "predictor"},
     "cfl": {"bytes": 36, "flops": 72},
 }
 
