@@ -462,9 +462,8 @@ mhd_status mhd_set_state(mhd_ctx* c, const double* src, int src_is_device)
     if (!c || !src) return MHD_E_INVAL;
     const size_t bytes = (size_t)c->n * c->nvar * sizeof(double);
     hipError_t e = hipSuccess;
-    // a state on the device (at a double's alignment) goes in and gives its time step in one
-    // pass
-    if (src_is_device && !((uintptr_t)src & 7u)) {
+    // a state on this device goes in and gives its time step in one pass
+    if (src_is_device && in_place(src, c->stream)) {
         Tick t(c, T_CFL);
         if (!c->is_mhd)
             return dev(launch_dust_load(c->geo, c->dp, c->fp32, src, c->reg[c->cur], c->partial, c->scalars,

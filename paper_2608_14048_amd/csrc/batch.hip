@@ -814,9 +814,9 @@ mhd_status mhd_batch_set_state(mhd_batch* c, const double* src, int src_is_devic
     if (!c || !src) return MHD_E_INVAL;
     hipError_t e = hipSuccess;
     const double* d = src;
-    // host memory (and device memory off a double's alignment) by way of the face area,
-    // which holds at least 8 doubles per cell
-    if (!src_is_device || ((uintptr_t)src & 7u)) {
+    // what the kernel may not read where it lies goes by way of the face area, which holds
+    // at least 8 doubles per cell
+    if (!src_is_device || !in_place(src, c->stream)) {
         e = hipMemcpyAsync(c->F, src, state_bytes(c), src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                            c->stream);
         d = (const double*)c->F;
@@ -832,7 +832,7 @@ mhd_status mhd_batch_set_state(mhd_batch* c, const double* src, int src_is_devic
 mhd_status mhd_batch_get_state(mhd_batch* c, double* dst, int dst_is_device)
 {
     if (!c || !dst) return MHD_E_INVAL;
-    const bool direct = dst_is_device && !((uintptr_t)dst & 7u);
+    const bool direct = dst_is_device && in_place(dst, c->stream);
     double* d = direct ? dst : (double*)c->F;
     hipError_t e = launch_batch_store(c->d_blk, c->nb, state_grid(c), c->fp32, c->reg[c->cur], d, c->stream);
     if (e == hipSuccess && !direct)

@@ -1004,6 +1004,13 @@ mhd_status mhd_cnn_accumulate(mhd_cnn* c, const double* state_t, const double* c
 {
     if (!c || !state_t || !coarse_next || !target || !(dt > 0.0) || !std::isfinite(dt)) return MHD_E_INVAL;
     hipError_t e = forward(c, state_t);
+    if (e == hipSuccess && !in_place(coarse_next, c->stream)) {
+        // by way of the second gradient buffer, whose 32 BF16 channels a voxel are 8 doubles
+        // (the backward pass writes it first after the residual is formed)
+        static_assert(kNPad * sizeof(bf16_t) == 8 * sizeof(double), "a canonical state");
+        e = hipMemcpyAsync(c->D1, coarse_next, (size_t)c->g.n * 8 * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
+        coarse_next = (const double*)c->D1;
+    }
     if (e != hipSuccess) return MHD_E_DEVICE;
     hipLaunchKernelGGL(k_residual, dim3(c->nblk), dim3(kThreads), 0, c->stream, c->g, c->O, c->scal + 16, c->sE, dt,
                        coarse_next, target, c->scal + 24, c->RW, c->partial);

@@ -160,6 +160,26 @@ hipError_t launch_dust_unpack(long long m, const void* reg, double* canon, hipSt
 
 inline unsigned int blocks_for(long long n) { return (unsigned int)((n + kBlock - 1) / kBlock); }
 
+// A caller's "device" pointer that kernels on stream s may read and write as doubles where
+// it lies: memory of the stream's own device, at a double's alignment.  Everything else that
+// a copy accepts (memory of another GPU, whether or not peer access is on, host and managed
+// memory, bytes off that alignment) has to go through a copy.
+inline bool in_place(const void* p, hipStream_t s)
+{
+    if ((uintptr_t)p & 7u) return false;
+    int dev = 0;
+    hipPointerAttribute_t a;
+    if (s) {
+        hipDevice_t sd = 0;
+        if (hipStreamGetDevice(s, &sd) != hipSuccess) return (void)hipGetLastError(), false;
+        dev = (int)sd;
+    } else if (hipGetDevice(&dev) != hipSuccess) {
+        return (void)hipGetLastError(), false;
+    }
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) return (void)hipGetLastError(), false;
+    return a.type == hipMemoryTypeDevice && !a.isManaged && a.device == dev;
+}
+
 // ---- what the closure step needs of a single-grid context (api.hip) ----
 struct CtxView {
     Geo geo;
