@@ -21,6 +21,10 @@
  *   - Memory: the caller owns the device workspace and the HIP stream; the library
  *     borrows both for the lifetime of the context and allocates no device memory.
  *     The context itself is a small host object freed by mhd_destroy.
+ *   - The states of mhd_set_state, mhd_get_state, mhd_batch_set_state and
+ *     mhd_batch_get_state may lie on any GPU of the process: on the stream's own GPU, at a
+ *     double's alignment, they are read or written where they lie, elsewhere through one
+ *     copy on the stream.  Every other device pointer belongs to the stream's GPU.
  *   - All work is enqueued on the caller's stream.  mhd_step is asynchronous;
  *     mhd_dt_cfl, mhd_diagnostics and transfers to or from host memory synchronise it.
  *   - Configuration is validated only in mhd_create (unsupported combinations are

@@ -461,7 +461,6 @@ mhd_status mhd_set_state(mhd_ctx* c, const double* src, int src_is_device)
 {
     if (!c || !src) return MHD_E_INVAL;
     const size_t bytes = (size_t)c->n * c->nvar * sizeof(double);
-    hipError_t e = hipSuccess;
     // a state on this device goes in and gives its time step in one pass
     if (src_is_device && in_place(src, c->stream)) {
         Tick t(c, T_CFL);
@@ -471,17 +470,11 @@ mhd_status mhd_set_state(mhd_ctx* c, const double* src, int src_is_device)
         return dev(launch_state_load(c->geo, c->mp, c->fp32, src, c->reg[c->cur], c->partial, c->scalars,
                                      c->cfl_scale, c->stream));
     }
-    // the canonical FP64 source on the device: the register (FP64 form) or the staging
-    // area (FP32 forms, or a host source that must be copied first)
-    const double* canon = src;
-    if (!c->fp32) {
-        e = hipMemcpyAsync(c->reg[c->cur], src, bytes,
-                           src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream);
-        canon = (const double*)c->reg[c->cur];
-    } else if (!src_is_device) {
-        e = hipMemcpyAsync(c->F, src, bytes, hipMemcpyHostToDevice, c->stream);
-        canon = (const double*)c->F;
-    }
+    // any other by way of a copy: into the register (FP64 form) or the staging area, which
+    // holds a canonical state (FP32 forms)
+    const double* canon = (const double*)(c->fp32 ? c->F : c->reg[c->cur]);
+    hipError_t e = hipMemcpyAsync((void*)canon, src, bytes,
+                                  src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess && !src_is_device) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return MHD_E_DEVICE;
     // the time step of the state as given, then (FP32 forms) its packed register
@@ -495,7 +488,7 @@ mhd_status mhd_get_state(mhd_ctx* c, double* dst, int dst_is_device)
     if (!c || !dst) return MHD_E_INVAL;
     const size_t bytes = (size_t)c->n * c->nvar * sizeof(double);
     hipError_t e;
-    if (c->fp32 && dst_is_device) {
+    if (c->fp32 && dst_is_device && in_place(dst, c->stream)) {
         e = unpack_reg(c, c->reg[c->cur], dst);
         return dev(e);
     }

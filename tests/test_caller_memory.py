@@ -45,6 +45,15 @@ def _bytes(name):
     return STATE * (2 if "batch" in name else 1)
 
 
+@pytest.mark.parametrize("kind,offset", [("own", 4)] + [(k, 0) for k in KINDS])
+def test_fp32_states_of_one_grid_go_through_the_staging_area(calls, kind, offset):
+    """Nor do the FP32 forms' kernels follow such a pointer, or one off a double's alignment."""
+    got = calls(kind, offset)
+    for who in ("fp32 mhd ", "fp32 dust "):
+        assert got[who + "set"].startswith(f"[in {STATE}]k"), got[who + "set"]
+        assert got[who + "get"] == f"k[out {STATE}]", got[who + "get"]
+
+
 @pytest.mark.parametrize("kind", KINDS)
 def test_foreign_memory_goes_through_one_copy(calls, kind):
     got = calls(kind)
@@ -59,5 +68,5 @@ def test_own_memory_is_read_in_place(calls):
     got = calls("own")
     for name in SETS:
         assert "[" not in got[name] and "k" in got[name], (name, got[name])
-    for name in ("fp64 batch get", "fp32 batch get"):
+    for name in ("fp64 batch get", "fp32 batch get", "fp32 mhd get", "fp32 dust get"):
         assert got[name] == "k", (name, got[name])
