@@ -141,8 +141,10 @@ __device__ __forceinline__ Raw<R> load_raw(const Geo& g, const RegView<R>& U, co
     return r;
 }
 
+// `odd` is set if one of them, or the pressure before its floor (which every stored value
+// enters), is not finite.
 template <class R>
-__device__ __forceinline__ Prim8<R> prims_of(const MhdParams& P, const Raw<R>& r)
+__device__ __forceinline__ Prim8<R> prims_of(const MhdParams& P, const Raw<R>& r, bool& odd)
 {
     // explicit roundings only: the same cell gives the same primitives at every call site
 #pragma clang fp contract(off)
@@ -162,6 +164,7 @@ __device__ __forceinline__ Prim8<R> prims_of(const MhdParams& P, const Raw<R>& r
     const double ke = 0.5 * dd * ((vx * vx + vy * vy) + vz * vz);
     const double me = 0.5 * ((bx * bx + by * by) + bz * bz);
     double pr = (P.gamma - 1.0) * ((r.E - ke) - me);
+    odd |= sizeof(R) == 8 ? !__builtin_isfinite(pr) : !(fabs(pr) <= 3.0e38);
     if (pr < P.p_floor) pr = P.p_floor;
     w.p = R(pr);
     return w;
@@ -169,9 +172,9 @@ __device__ __forceinline__ Prim8<R> prims_of(const MhdParams& P, const Raw<R>& r
 
 template <class R>
 __device__ __forceinline__ Prim8<R> load_prims(const Geo& g, const MhdParams& P, const RegView<R>& U,
-                                               const Column& q, int z)
+                                               const Column& q, int z, bool& odd)
 {
-    return prims_of(P, load_raw(g, U, q, z));
+    return prims_of(P, load_raw(g, U, q, z), odd);
 }
 
 // A value that is the same in every lane, held in a scalar register (converted from the
@@ -205,7 +208,9 @@ template <class R>
 struct ZPipe<0, R> {
     static constexpr int AHEAD = 0, PRIME = 1;  // plane k0-1 before the march
     R prev;
+    template <bool>
     __device__ void prime(const R* a) { prev = a[0]; }
+    template <bool>
     __device__ void push(R ak, R, R& aL, R& aR)
     {
         aL = prev;
@@ -220,12 +225,14 @@ template <class R>
 struct ZPipe<1, R> {
     static constexpr int AHEAD = 1, PRIME = 3;  // planes k0-2 .. k0
     R am, a0, apl;  // a(k-1), a(k), a_+(k-1)
+    template <bool>
     __device__ void prime(const R* a)
     {
         apl = fma_r(R(0.5), slope_vl(a[0], a[1], a[2]), a[1]);
         am = a[1];
         a0 = a[2];
     }
+    template <bool>
     __device__ void push(R, R a, R& aL, R& aR)
     {
         const R d = slope_vl(am, a0, a);
@@ -241,26 +248,28 @@ template <class R>
 struct ZPipe<2, R> {
     static constexpr int AHEAD = 2, PRIME = 5;  // planes k0-3 .. k0+1
     R a1, m0, ilo, apl;  // a(k+1), slope(k), a_{k-1/2}, a_+(k-1)
+    template <bool ODD>
     __device__ void prime(const R* a)
     {
-        const R s1 = cw_slope(a[0], a[1], a[2]);
-        const R s2 = cw_slope(a[1], a[2], a[3]);
-        const R s3 = cw_slope(a[2], a[3], a[4]);
+        const R s1 = cw_slope<ODD>(a[0], a[1], a[2]);
+        const R s2 = cw_slope<ODD>(a[1], a[2], a[3]);
+        const R s3 = cw_slope<ODD>(a[2], a[3], a[4]);
         R lo = cw_interface(a[1], a[2], s1, s2);  // a_{k0-3/2}
         R hi = cw_interface(a[2], a[3], s2, s3);  // a_{k0-1/2}
         ilo = hi;
-        cw_limit(a[2], lo, hi);                   // cell k0-1
+        cw_limit<ODD>(a[2], lo, hi);              // cell k0-1
         apl = hi;
         a1 = a[4];
         m0 = s3;
     }
+    template <bool ODD>
     __device__ void push(R ak, R a, R& aL, R& aR)
     {
-        const R m1 = cw_slope(ak, a1, a);         // slope of cell k+1
+        const R m1 = cw_slope<ODD>(ak, a1, a);    // slope of cell k+1
         R lo = ilo;
         R hi = cw_interface(ak, a1, m0, m1);      // a_{k+1/2}
         ilo = hi;
-        cw_limit(ak, lo, hi);                     // cell k
+        cw_limit<ODD>(ak, lo, hi);                // cell k
         aL = apl;
         aR = lo;
         apl = hi;
@@ -276,25 +285,27 @@ template <class R>
 struct ZPipeLean {
     static constexpr int AHEAD = 2, PRIME = 5;  // planes k0-3 .. k0+1
     R m0, ilo, apl;  // slope(k), a_{k-1/2}, a_+(k-1)
+    template <bool ODD>
     __device__ void prime(const R* a)
     {
-        const R s1 = cw_slope(a[0], a[1], a[2]);
-        const R s2 = cw_slope(a[1], a[2], a[3]);
-        const R s3 = cw_slope(a[2], a[3], a[4]);
+        const R s1 = cw_slope<ODD>(a[0], a[1], a[2]);
+        const R s2 = cw_slope<ODD>(a[1], a[2], a[3]);
+        const R s3 = cw_slope<ODD>(a[2], a[3], a[4]);
         R lo = cw_interface(a[1], a[2], s1, s2);  // a_{k0-3/2}
         R hi = cw_interface(a[2], a[3], s2, s3);  // a_{k0-1/2}
         ilo = hi;
-        cw_limit(a[2], lo, hi);                   // cell k0-1
+        cw_limit<ODD>(a[2], lo, hi);              // cell k0-1
         apl = hi;
         m0 = s3;
     }
+    template <bool ODD>
     __device__ void push(R ak, R a1, R a, R& aL, R& aR)
     {
-        const R m1 = cw_slope(ak, a1, a);         // slope of cell k+1
+        const R m1 = cw_slope<ODD>(ak, a1, a);    // slope of cell k+1
         R lo = ilo;
         R hi = cw_interface(ak, a1, m0, m1);      // a_{k+1/2}
         ilo = hi;
-        cw_limit(ak, lo, hi);                     // cell k
+        cw_limit<ODD>(ak, lo, hi);                // cell k
         aL = apl;
         aR = lo;
         apl = hi;
@@ -367,6 +378,12 @@ struct FluxTile {
     // XCD do not stay in its L2 from one pass to the next: 512 x 512 x 256 FP64 PLM + HLLE,
     // bandwidth-bound, 5.77 + 6.51 -> 5.40 + 5.67 ms, the donor cell's kept fields aside)
     static constexpr bool kCarry = RECON == 1;
+    // PPM: a tile that met a value which is not finite is marched again with ODD (over the
+    // same outputs; nothing it reads has changed), so that every other tile pays only a
+    // comparison per loaded cell and a barrier: 256^3 corrector 2078 us either way, FP32
+    // blocks of 64^3 and less 1 to 2 % slower.  Deciding on the spot, per limiter or per
+    // variable, cost 1 to 2 % at 256^3 and spilled as much.
+    static constexpr bool kCheck = RECON == 2;
     // halo cells of a staged plane: HX columns beside the tile's rows, as many rows above
     // and below its columns (no corners)
     static constexpr int HX = SL + SR + 1, NH = HX * (TX + TY);
@@ -384,12 +401,13 @@ struct FluxTile {
         R sw[8][LY][LX];         // primitives of the plane
         R hx[5][TY][TX + 1];     // fluxes through the x faces of the plane's rows
         R hy[5][TY + 1][TX];     // fluxes through the y faces of the plane's columns
+        int odd;                 // kCheck: a value of the tile or its stencil is not finite
         Kept kept;
     };
 
     // Face states of the seven face-frame variables from a stencil line in LDS: `at(v, s)`
     // gives staged variable v at offset s from the face's high-side cell.
-    template <class At>
+    template <bool ODD, class At>
     __device__ static void recon7(const int comp[7], At at, Prim7<R>& L, Prim7<R>& Rt)
     {
         R* lr[7][2] = {{&L.d, &Rt.d}, {&L.vn, &Rt.vn}, {&L.vt1, &Rt.vt1}, {&L.vt2, &Rt.vt2},
@@ -399,7 +417,7 @@ struct FluxTile {
         for (int v = 0; v < 7; ++v) {
     #pragma unroll
             for (int s = -SL; s <= SR; ++s) st[3 + s] = at(comp[v], s);
-            face_states<RECON>(st, *lr[v][0], *lr[v][1]);
+            face_states<RECON, ODD>(st, *lr[v][0], *lr[v][1]);
             if constexpr (kFence) {
                 pin(*lr[v][0], *lr[v][1]);
                 __builtin_amdgcn_sched_barrier(0);
@@ -410,9 +428,20 @@ struct FluxTile {
     __device__ static void run(const Geo& g, const MhdParams& P, const StageArgs<R>& a, int x0, int y0,
                                int k0, int k1, Lds& lds)
     {
+        if (march<false>(g, P, a, x0, y0, k0, k1, lds) && kCheck) march<true>(g, P, a, x0, y0, k0, k1, lds);
+    }
+
+    template <bool ODD>
+    __device__ static bool march(const Geo& g, const MhdParams& P, const StageArgs<R>& a, int x0, int y0,
+                                 int k0, int k1, Lds& lds)
+    {
         using Pipe = std::conditional_t<kLean, ZPipeLean<R>, ZPipe<RECON, R>>;
         auto& sw = lds.sw;
-        const int lane = (int)threadIdx.x % TX, row = (int)threadIdx.x / TX;
+        // (read anew by each march: nothing derived from it is kept through the first for a
+        // second one)
+        int tid = (int)threadIdx.x;
+        if constexpr (kCheck) asm volatile("" : "+v"(tid));
+        const int lane = tid % TX, row = tid / TX;
         const int i = x0 + lane, j = y0 + row;
         const bool live = i < g.nx && j < g.ny;
         // this thread's cell, taken periodically (a lane or row just past the grid edge
@@ -428,23 +457,25 @@ struct FluxTile {
         R* Fo[NFACE];
     #pragma unroll
         for (int q = 0; q < NFACE; ++q) Fo[q] = a.F + q * n;
-        const int wave = (int)threadIdx.x / 64, wl = (int)threadIdx.x % 64;
+        const int wave = tid / 64, wl = tid % 64;
 
         // z pipeline of the face-frame variables (rho, v_z, v_x, v_y, p, B_x, B_y); plane
         // k's own values come from the staged plane (a direct load on the last pass)
+        bool bad = false;  // this lane has loaded a value that is not finite
+        if (kCheck && !ODD && tid == 0) lds.odd = 0;
         Pipe zp[7];
         R bzk = R(0);  // kCarry: B_z of plane k, beside the pipeline's seven variables
         {
             R pre[7][Pipe::PRIME];
     #pragma unroll
             for (int s = 0; s < Pipe::PRIME; ++s) {
-                const Prim8<R> w = load_prims(g, P, a.in, own, wrap_any(k0 - Pipe::PRIME + Pipe::AHEAD + s, g.nz));
+                const Prim8<R> w = load_prims(g, P, a.in, own, wrap_any(k0 - Pipe::PRIME + Pipe::AHEAD + s, g.nz), bad);
                 pre[0][s] = w.d; pre[1][s] = w.vz; pre[2][s] = w.vx; pre[3][s] = w.vy;
                 pre[4][s] = w.p; pre[5][s] = w.bx; pre[6][s] = w.by;
                 bzk = w.bz;
             }
     #pragma unroll
-            for (int v = 0; v < 7; ++v) zp[v].prime(pre[v]);
+            for (int v = 0; v < 7; ++v) zp[v].template prime<ODD>(pre[v]);
         }
         const double bdt = a.co.bdt, g0 = a.co.g0, g1 = a.co.g1;
         const R bdtr = uniform(R(bdt)), g0r = uniform(R(g0)), g1r = uniform(R(g1));
@@ -467,6 +498,7 @@ struct FluxTile {
             const bool full = k < k1;
             Prim8<R> wk{}, wz{}, wz1{};
             Raw<R> rk;
+            bool dup = false;  // (of cells that the pipeline has seen)
             // stage the primitives of plane k; the staging waves get issue priority so their
             // loads go out ahead of the arithmetic of the other workgroups on the CU
             if (full) __builtin_amdgcn_s_setprio(1);
@@ -477,10 +509,10 @@ struct FluxTile {
                 wk.p = zp[4].a0; wk.bx = zp[5].a0; wk.by = zp[6].a0; wk.bz = bzk;
             } else {
                 rk = load_raw(g, a.in, own, wrap_any(k, g.nz));
-                wk = prims_of(P, rk);
+                wk = prims_of(P, rk, dup);
             }
-            if constexpr (Pipe::AHEAD > 0) wz = load_prims(g, P, a.in, own, wrap_any(k + Pipe::AHEAD, g.nz));
-            if constexpr (kLean) wz1 = load_prims(g, P, a.in, own, wrap_any(k + 1, g.nz));
+            if constexpr (Pipe::AHEAD > 0) wz = load_prims(g, P, a.in, own, wrap_any(k + Pipe::AHEAD, g.nz), bad);
+            if constexpr (kLean) wz1 = load_prims(g, P, a.in, own, wrap_any(k + 1, g.nz), dup);
             if (full) {
                 auto put = [&](int r, int cc, const Prim8<R>& w) {
                     sw[0][r][cc] = w.d; sw[1][r][cc] = w.vx; sw[2][r][cc] = w.vy; sw[3][r][cc] = w.vz;
@@ -494,12 +526,12 @@ struct FluxTile {
                     const int e = hr < SL ? hr : hr + (yh ? TY : TX);
                     const int r = yh ? e : hc + SL, cc = yh ? hc + SL : e;
                     const int gx = wrap_any(x0 + cc - SL, g.nx), gy = wrap_any(y0 + r - SL, g.ny);
-                    put(r, cc, load_prims(g, P, a.in, column(g, gx, gy), k));
+                    put(r, cc, load_prims(g, P, a.in, column(g, gx, gy), k, bad));
                 };
                 if constexpr (NH <= NT) {
-                    if ((int)threadIdx.x < NH) halo((int)threadIdx.x);
+                    if (tid < NH) halo(tid);
                 } else {
-                    for (int t = threadIdx.x; t < NH; t += NT) halo(t);
+                    for (int t = tid; t < NH; t += NT) halo(t);
                 }
             }
             if (full) {
@@ -515,9 +547,9 @@ struct FluxTile {
             {
                 auto push = [&](Pipe& zpv, R ak, R a1, R a2, R& l, R& r) {
                     if constexpr (kLean)
-                        zpv.push(ak, a1, a2, l, r);
+                        zpv.template push<ODD>(ak, a1, a2, l, r);
                     else
-                        zpv.push(ak, a2, l, r);
+                        zpv.template push<ODD>(ak, a2, l, r);
                     if constexpr (kFence) {
                         pin(r, zpv.apl);
                         pin(zpv.ilo, zpv.m0);
@@ -576,8 +608,8 @@ struct FluxTile {
                     double Ei, Eb;
                     if constexpr (RECON == 0) {
     #pragma unroll
-                        for (int v = 0; v < 4; ++v) ci[v] = lds.kept.u[v][threadIdx.x];
-                        Ei = lds.kept.E[threadIdx.x];
+                        for (int v = 0; v < 4; ++v) ci[v] = lds.kept.u[v][tid];
+                        Ei = lds.kept.E[tid];
                     } else if (IN) {
                         ci[0] = ldT(a.in.rho, cb);
     #pragma unroll
@@ -618,10 +650,10 @@ struct FluxTile {
             }
             if (!full) break;
             if constexpr (RECON == 0) {
-                lds.kept.u[0][threadIdx.x] = rk.rho;
+                lds.kept.u[0][tid] = rk.rho;
     #pragma unroll
-                for (int v = 0; v < 3; ++v) lds.kept.u[1 + v][threadIdx.x] = rk.m[v];
-                lds.kept.E[threadIdx.x] = rk.E;
+                for (int v = 0; v < 3; ++v) lds.kept.u[1 + v][tid] = rk.m[v];
+                lds.kept.E[tid] = rk.E;
             }
             // lean form: every thread has read the fluxes of plane k - 1 before any
             // thread overwrites them with those of plane k
@@ -630,7 +662,7 @@ struct FluxTile {
             // ---- x face (low face of the cell): (rho, vx, vy, vz, p, By, Bz)
             if (xneed) {
                 const int comp[7] = {0, 1, 2, 3, 4, 6, 7};
-                recon7(comp, [&](int v, int s) { return sw[v][row + SL][lane + SL + s]; }, L, Rt);
+                recon7<ODD>(comp, [&](int v, int s) { return sw[v][row + SL][lane + SL + s]; }, L, Rt);
                 solve<RS>(L, Rt, ldT(a.in.b[0], c), P, f);
                 lds.hx[0][row][lane] = f.d; lds.hx[1][row][lane] = f.mn; lds.hx[2][row][lane] = f.mt1;
                 lds.hx[3][row][lane] = f.mt2; lds.hx[4][row][lane] = f.e;
@@ -643,7 +675,7 @@ struct FluxTile {
             // ---- y face: (rho, vy, vz, vx, p, Bz, Bx)
             if (yneed) {
                 const int comp[7] = {0, 2, 3, 1, 4, 7, 5};
-                recon7(comp, [&](int v, int s) { return sw[v][row + SL + s][lane + SL]; }, L, Rt);
+                recon7<ODD>(comp, [&](int v, int s) { return sw[v][row + SL + s][lane + SL]; }, L, Rt);
                 solve<RS>(L, Rt, ldT(a.in.b[1], c), P, f);
                 lds.hy[0][row][lane] = f.d; lds.hy[1][row][lane] = f.mt2; lds.hy[2][row][lane] = f.mn;
                 lds.hy[3][row][lane] = f.mt1; lds.hy[4][row][lane] = f.e;
@@ -691,7 +723,7 @@ struct FluxTile {
                     const int base = ry ? (TY + SL) * LX + rq + SL : (rq + SL) * LX + TX + SL;
                     const int stride = ry ? LX : 1;
                     const R* swf = &sw[0][0][0];
-                    recon7(comp, [&](int v, int s) { return swf[v * (LY * LX) + base + s * stride]; }, L, Rt);
+                    recon7<ODD>(comp, [&](int v, int s) { return swf[v * (LY * LX) + base + s * stride]; }, L, Rt);
                     // (the offset and not the pointer picked per lane: a table of the two
                     // pointers would live in scratch memory)
                     const long long by = a.in.b[1] - a.in.b[0];
@@ -725,6 +757,10 @@ struct FluxTile {
             // every thread finished reading before the barrier above, and the fluxes are
             // rewritten only after the next barrier
         }
+        if constexpr (!kCheck || ODD) return false;
+        if (bad) *(volatile int*)&lds.odd = 1;
+        __syncthreads();
+        return *(volatile int*)&lds.odd != 0;
     }
 };
 

@@ -110,21 +110,39 @@ __device__ __forceinline__ R slope_vl(R am, R a0, R ap)
     }
 }
 
+// PPM beside values that are not finite (ODD: there may be one).  A neighbourhood with an
+// infinity or a not-a-number keeps Colella and Woodward's conditions as they are written,
+// where a false comparison gives a zero slope and leaves a parabola's edges alone, so that a
+// bad cell makes the face states on both its sides bad; minima, maxima and medians would
+// drop it and hand the cell beside it a finite edge.  Each lane looks at its own values:
+// finite neighbourhoods give the same bits with ODD and without.
+template <class R>
+__device__ __forceinline__ bool all_finite(R a, R b, R c)
+{
+    return __builtin_isfinite(a) && __builtin_isfinite(b) && __builtin_isfinite(c);
+}
+
 // Half of Colella and Woodward's limited central slope of the middle cell: the value of
 // least magnitude of (ap - am)/4, ap - a0 and a0 - am, or 0 unless the last two share a
 // sign (the quarter is exact).  Minima, maxima and medians only: ten FP64 or six FP32
 // instructions, against twelve with a product's sign, a select and a copied sign.
-template <class R>
+template <bool ODD, class R>
 __device__ __forceinline__ R cw_slope(R am, R a0, R ap)
 {
 #pragma clang fp contract(off)
     const R dm = a0 - am, dp = ap - a0, c = R(0.25) * (ap - am);
+    R s;
     if constexpr (sizeof(R) == 4) {
-        return __builtin_amdgcn_fmed3f(c, __builtin_amdgcn_fmed3f(dm, dp, 0.0f), 0.0f);
+        s = __builtin_amdgcn_fmed3f(c, __builtin_amdgcn_fmed3f(dm, dp, 0.0f), 0.0f);
     } else {
         const R up = max_r(min_r(dm, dp), R(0)), dn = min_r(max_r(dm, dp), R(0));
-        return max_r(min_r(c, up), dn);
+        s = max_r(min_r(c, up), dn);
     }
+    if (ODD && !all_finite(am, a0, ap)) {
+        const R lim = min_r(abs_r(c), min_r(abs_r(dm), abs_r(dp)));
+        s = dm * dp > R(0) ? (c > R(0) ? lim : -lim) : R(0);
+    }
+    return s;
 }
 
 // Colella-Woodward interface value between cells a0 and a1 from the halves m0, m1 of
@@ -151,24 +169,36 @@ __device__ __forceinline__ double cw_edge(double a, double edge, double other)
 // branch (against branches on the conditions, 256^3 VL2 + HLLD corrector, with the slopes
 // above: FP64 2357 -> 2078 us, FP32 1142 -> 1034; a caller that needs one edge costs one).
 // FP64: medians.  FP32: the conditions as written, whose rounding decides which edge moves.
-__device__ __forceinline__ void cw_limit(double a, double& lo, double& hi)
-{
-    const double l = cw_edge(a, lo, hi);
-    hi = cw_edge(a, hi, lo);
-    lo = l;
-}
-__device__ __forceinline__ void cw_limit(float a, float& lo, float& hi)
+template <class R>
+__device__ __forceinline__ void cw_conditions(R a, R& lo, R& hi)
 {
 #pragma clang fp contract(off)
-    const bool flat = (hi - a) * (a - lo) <= 0.0f;
-    const float da = hi - lo;
-    const float a6 = 6.0f * fma_r(-0.5f, lo + hi, a);
-    const float da2 = da * da;
-    const float p = da * a6;
-    const float l = p > da2 ? fma_r(-2.0f, hi, 3.0f * a) : lo;
-    const float h = -da2 > p ? fma_r(-2.0f, lo, 3.0f * a) : hi;
+    const bool flat = (hi - a) * (a - lo) <= R(0);
+    const R da = hi - lo;
+    const R a6 = R(6) * fma_r(R(-0.5), lo + hi, a);
+    const R da2 = da * da;
+    const R p = da * a6;
+    const R l = p > da2 ? fma_r(R(-2), hi, R(3) * a) : lo;
+    const R h = -da2 > p ? fma_r(R(-2), lo, R(3) * a) : hi;
     lo = flat ? a : l;
     hi = flat ? a : h;
+}
+template <bool ODD>
+__device__ __forceinline__ void cw_limit(double a, double& lo, double& hi)
+{
+    double l = cw_edge(a, lo, hi), h = cw_edge(a, hi, lo);
+    if (ODD && !all_finite(a, lo, hi)) {
+        l = lo;
+        h = hi;
+        cw_conditions(a, l, h);
+    }
+    lo = l;
+    hi = h;
+}
+template <bool ODD>
+__device__ __forceinline__ void cw_limit(float a, float& lo, float& hi)
+{
+    cw_conditions(a, lo, hi);
 }
 
 template <int RECON, class R>
@@ -176,6 +206,7 @@ struct FaceStates;
 
 template <class R>
 struct FaceStates<0, R> {
+    template <bool ODD>
     __device__ static void get(const R* s, R& aL, R& aR)
     {
         aL = s[2];
@@ -185,6 +216,7 @@ struct FaceStates<0, R> {
 
 template <class R>
 struct FaceStates<1, R> {
+    template <bool ODD>
     __device__ static void get(const R* s, R& aL, R& aR)
     {
         aL = fma_r(R(0.5), slope_vl(s[1], s[2], s[3]), s[2]);
@@ -195,30 +227,32 @@ struct FaceStates<1, R> {
 // PPM: the three interface values around the two cells next to the face are shared.
 template <class R>
 struct FaceStates<2, R> {
+    template <bool ODD>
     __device__ static void get(const R* s, R& aL, R& aR)
     {
-        const R m1 = cw_slope(s[0], s[1], s[2]);
-        const R m2 = cw_slope(s[1], s[2], s[3]);
-        const R m3 = cw_slope(s[2], s[3], s[4]);
-        const R m4 = cw_slope(s[3], s[4], s[5]);
+        const R m1 = cw_slope<ODD>(s[0], s[1], s[2]);
+        const R m2 = cw_slope<ODD>(s[1], s[2], s[3]);
+        const R m3 = cw_slope<ODD>(s[2], s[3], s[4]);
+        const R m4 = cw_slope<ODD>(s[3], s[4], s[5]);
         const R i0 = cw_interface(s[1], s[2], m1, m2);  // a_{f-3/2}
         const R i1 = cw_interface(s[2], s[3], m2, m3);  // a_{f-1/2}
         const R i2 = cw_interface(s[3], s[4], m3, m4);  // a_{f+1/2}
         R lo = i0, hi = i1;
-        cw_limit(s[2], lo, hi);
+        cw_limit<ODD>(s[2], lo, hi);
         aL = hi;
         lo = i1;
         hi = i2;
-        cw_limit(s[3], lo, hi);
+        cw_limit<ODD>(s[3], lo, hi);
         aR = lo;
     }
 };
 
-// Face states of the six cells s[0..5] around the face between s[2] and s[3].
-template <int RECON, class R>
+// Face states of the six cells s[0..5] around the face between s[2] and s[3] (ODD: a value
+// that is not finite may be among them).
+template <int RECON, bool ODD, class R>
 __device__ __forceinline__ void face_states(const R* s, R& aL, R& aR)
 {
-    FaceStates<RECON, R>::get(s, aL, aR);
+    FaceStates<RECON, R>::template get<ODD>(s, aL, aR);
 }
 
 // ----------------------------------------------------------------------------------
