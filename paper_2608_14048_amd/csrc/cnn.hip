@@ -153,7 +153,10 @@ __global__ __launch_bounds__(kThreads) void k_cnn_input(Geo g, double gamma, con
 // two blocks, 4 the weights, 10 the matrix instructions and their LDS reads).  The weight
 // fragments are the first operand where the output is channel-last, so that a lane ends
 // up with four channels of a voxel and stores 8 bytes.
-constexpr int kTileY = 4, kTileZ = 8;
+//
+// A block is GY x GZ groups of WY rows x WZ planes, two waves each: 2 x 4 (four rows, eight
+// planes) above; a grid of few planes, or few rows, takes 32 rows of one plane, or one row
+// of 32 planes, where 4 x 8 blocks would be mostly padding (see conv).
 constexpr int kConvThreads = 512, kConvWaves = kConvThreads / 64;
 constexpr int kConvGroups = 256;  // persistent workgroups at most: one per CU
 
@@ -174,7 +177,7 @@ struct ConvFrag<16> {
     __device__ static f4 mma(T a, T b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0); }
 };
 
-template <int CINP, int MODE>
+template <int CINP, int MODE, int WY, int WZ, int GY, int GZ>
 __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_conv(
     Geo g, const bf16_t* __restrict__ X, const bf16_t* __restrict__ B, const float* __restrict__ bias,
     const bf16_t* __restrict__ M, bf16_t* __restrict__ Y, float* __restrict__ O, int nstore, unsigned int nty,
@@ -184,7 +187,10 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2)
     using T = typename Frag::T;
     constexpr int KL = CINP / 4;                     // K values of a lane
     constexpr int CH = CINP / 8;                     // 16-byte chunks of a voxel
-    constexpr int HY = kTileY + 2, HZ = kTileZ + 2, ROWS = HY * HZ;
+    static_assert(2 * GY * GZ == kConvWaves && WY * WZ == 8, "two waves a group, eight rows a wave");
+    constexpr int TY = WY * GY, TZ = WZ * GZ;        // rows and planes of a block
+    constexpr int HY = TY + 2, HZ = TZ + 2, ROWS = HY * HZ;
+    constexpr int VY = WY + 2, VZ = WZ + 2;          // a wave's rows and planes with their halo
     constexpr int NR = (ROWS + kConvWaves - 1) / kConvWaves;
     // a wave stages rows w, w + 8, ..: one load for a row's first 16 voxels (all 18 where
     // they fit the 64 lanes), and one for the last two voxels of eight rows
@@ -194,7 +200,8 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2)
     __shared__ __align__(16) bf16_t sA[18 * ROWS * CINP];
     auto swz = [](int x) { return CINP == 32 ? (x >> 2) & 3 : (x >> 3) & 1; };
     const int lane = (int)threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int zp = 2 * (w >> 1), cb = w & 1;  // this wave's planes (zp, zp + 1) and channel half
+    // this wave's first row and plane in the block, and its channel half
+    const int yp = (w >> 1) % GY * WY, zp = (w >> 1) / GY * WZ, cb = w & 1;
     const int lr = lane & 15, lg = lane >> 4;
     const unsigned int ntx = (unsigned int)g.nx / 16u, n = (unsigned int)g.n;
 
@@ -202,8 +209,8 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2)
     const int tvox = 16 + (lane >> 2 & 1), tpos = lane & 3;  // and of a row's tail
     u4 v[NR], tail[NTAIL > 0 ? NTAIL : 1];
     auto fetch = [&](unsigned int blk) {
-        const int x0 = (int)(blk % ntx) * 16, y0 = (int)((blk / ntx) % nty) * kTileY;
-        const int z0 = (int)(blk / (ntx * nty)) * kTileZ;
+        const int x0 = (int)(blk % ntx) * 16, y0 = (int)((blk / ntx) % nty) * TY;
+        const int z0 = (int)(blk / (ntx * nty)) * TZ;
         // first voxel of halo row r of the block (periodic)
         auto line = [&](int r) {
             int y = y0 + r % HY - 1, z = z0 + r / HY - 1;
@@ -242,7 +249,7 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
     for (int dx = 0; dx < 3; ++dx) {
         const int x = lr + dx, chunk = CINP == 32 ? lg : lg >> 1, part = CINP == 32 ? 0 : (lg & 1) * 4;
-        a0[dx] = sA + (zp * HY * 18 + x) * CINP + (chunk ^ swz(x)) * 8 + part;
+        a0[dx] = sA + ((zp * HY + yp) * 18 + x) * CINP + (chunk ^ swz(x)) * 8 + part;
     }
 
     for (unsigned int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
@@ -260,32 +267,34 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2)
         __syncthreads();
         if (blk + gridDim.x < nblk) fetch(blk + gridDim.x);
 
-        // acc[rb]: row rb % 4 of plane zp + rb / 4
+        // acc[rb]: row yp + rb % WY of plane zp + rb / WY
         f4 acc[8];
 #pragma unroll
         for (int rb = 0; rb < 8; ++rb) acc[rb] = f4{0.f, 0.f, 0.f, 0.f};
-        // the fragments of input row r (row r % HY of plane zp + r / HY of the halo block),
-        // one per dx; those of row r + 1 are read while row r multiplies
-        auto row = [&](int r, int dx) { return *reinterpret_cast<const T*>(a0[dx] + r * (18 * CINP)); };
+        // the fragments of input row r (row yp + r % VY of plane zp + r / VY of the halo
+        // block), one per dx; those of row r + 1 are read while row r multiplies
+        auto row = [&](int r, int dx) {
+            return *reinterpret_cast<const T*>(a0[dx] + (r / VY * HY + r % VY) * (18 * CINP));
+        };
         T cur[3], nxt[3];
 #pragma unroll
         for (int dx = 0; dx < 3; ++dx) cur[dx] = nxt[dx] = row(0, dx);
 #pragma unroll
-        for (int r = 0; r < 4 * HY; ++r) {
-            if (r + 1 < 4 * HY) {
+        for (int r = 0; r < VY * VZ; ++r) {
+            if (r + 1 < VY * VZ) {
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) nxt[dx] = row(r + 1, dx);
             }
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-                for (int z = 0; z < 2; ++z)
+                for (int z = 0; z < WZ; ++z)
 #pragma unroll
-                    for (int y = 0; y < kTileY; ++y) {
-                        const int dz = r / HY - z, dy = r % HY - y;
+                    for (int y = 0; y < WY; ++y) {
+                        const int dz = r / VY - z, dy = r % VY - y;
                         if (dz < 0 || dz > 2 || dy < 0 || dy > 2) continue;
                         const int t = dz * 9 + dy * 3 + dx;
-                        f4& d = acc[z * 4 + y];
+                        f4& d = acc[z * WY + y];
                         d = MODE == 1 ? Frag::mma(cur[dx], wt[t], d) : Frag::mma(wt[t], cur[dx], d);
                     }
 #pragma unroll
@@ -294,11 +303,11 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(2)
         }
         // MODE 1: element i of lane l is voxel 4 (l / 16) + i of the row, channel l % 16;
         // else voxel l % 16, channel 4 (l / 16) + i: four voxels or four channels per store
-        const int x0 = (int)(blk % ntx) * 16, y0 = (int)((blk / ntx) % nty) * kTileY;
-        const int z0 = (int)(blk / (ntx * nty)) * kTileZ + zp;
+        const int x0 = (int)(blk % ntx) * 16, y0 = (int)((blk / ntx) % nty) * TY + yp;
+        const int z0 = (int)(blk / (ntx * nty)) * TZ + zp;
 #pragma unroll
         for (int rb = 0; rb < 8; ++rb) {
-            const int y = y0 + rb % 4, z = z0 + rb / 4;
+            const int y = y0 + rb % WY, z = z0 + rb / WY;
             if (y >= g.ny || z >= g.nz) continue;
             const unsigned int vrow = ((unsigned int)z * (unsigned int)g.ny + (unsigned int)y) * (unsigned int)g.nx +
                                       (unsigned int)x0;
@@ -806,16 +815,39 @@ hipError_t pack_all(mhd_cnn* c)
     return hipGetLastError();
 }
 
-// One convolution launch.
+// One convolution launch on blocks of WY GY rows x WZ GZ planes.
+template <int CINP, int MODE, int WY, int WZ, int GY, int GZ>
+void conv_blocks(const mhd_cnn* c, const bf16_t* X, const bf16_t* B, const float* bias, const bf16_t* M, bf16_t* Y,
+                 float* O, int nstore)
+{
+    const unsigned int nty = (unsigned int)((c->g.ny + WY * GY - 1) / (WY * GY));
+    const unsigned int nblk = (unsigned int)(c->g.nx / 16) * nty * (unsigned int)((c->g.nz + WZ * GZ - 1) / (WZ * GZ));
+    const unsigned int grid = nblk < (unsigned int)kConvGroups ? nblk : (unsigned int)kConvGroups;
+    hipLaunchKernelGGL((k_conv<CINP, MODE, WY, WZ, GY, GZ>), dim3(grid), dim3(kConvThreads), 0, c->stream, c->g, X, B,
+                       bias, M, Y, O, nstore, nty, nblk);
+}
+
+// One convolution.  All block shapes give the same bits; a flat one, whose halo has 102 rows
+// against 60, takes about 1.6 times as long, so it is chosen where it needs at most 5/8 of
+// the rounds of workgroups.  The network's forward pass with 4 x 8 blocks only, with the
+// flat ones, and with a wave per 64 voxels and no blocks (us): 512 x 512 x 1 362, 96, 174;
+// 512 x 1 x 512 198, 94, 173; 512 x 512 x 3 354, 267, 463; 512 x 5 x 512 431, 350, 741;
+// 64 x 64 x 2, a single round, 40, 49, 69.
 template <int CINP, int MODE>
 void conv(const mhd_cnn* c, const bf16_t* X, const bf16_t* B, const float* bias, const bf16_t* M, bf16_t* Y,
           float* O, int nstore)
 {
-    const unsigned int nty = (unsigned int)((c->g.ny + kTileY - 1) / kTileY);
-    const unsigned int nblk = (unsigned int)(c->g.nx / 16) * nty * (unsigned int)((c->g.nz + kTileZ - 1) / kTileZ);
-    const unsigned int grid = nblk < (unsigned int)kConvGroups ? nblk : (unsigned int)kConvGroups;
-    hipLaunchKernelGGL((k_conv<CINP, MODE>), dim3(grid), dim3(kConvThreads), 0, c->stream, c->g, X, B, bias, M, Y, O,
-                       nstore, nty, nblk);
+    const long long ntx = c->g.nx / 16, ny = c->g.ny, nz = c->g.nz;
+    auto rounds = [&](int ty, int tz) {
+        return (ntx * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz) + kConvGroups - 1) / kConvGroups;
+    };
+    const long long tall = rounds(4, 8), row = rounds(32, 1), plane = rounds(1, 32);
+    if (8 * row <= 5 * tall && row <= plane)
+        conv_blocks<CINP, MODE, 8, 1, 4, 1>(c, X, B, bias, M, Y, O, nstore);
+    else if (8 * plane <= 5 * tall)
+        conv_blocks<CINP, MODE, 1, 8, 1, 4>(c, X, B, bias, M, Y, O, nstore);
+    else
+        conv_blocks<CINP, MODE, 4, 2, 1, 4>(c, X, B, bias, M, Y, O, nstore);
 }
 
 // forward pass from a canonical state; keeps every layer input for the backward pass
