@@ -305,6 +305,12 @@ struct mhd_batch {
     int nb;
     std::vector<Geo> geo;
     std::vector<unsigned long long> off;
+    // blocks that lie one after the other in the registers as in a state: first cell in
+    // either, cells
+    struct Run {
+        unsigned long long off, at, n;
+    };
+    std::vector<Run> runs;
     unsigned long long ncell;  // padded total
     mhd_physics phys;
     mhd_scheme scheme;
@@ -692,6 +698,16 @@ int state_grid(const mhd_batch* c)
     return (int)std::max(1LL, std::min((8191LL + c->nb) / c->nb, cap));
 }
 
+// Whether a state of all blocks leaves the FP64 register by copies of its runs: on its own,
+// or with 2^21 cells and more to a run (134 MB).  A copy is 8 % faster than the kernel that
+// stores all blocks but costs a call of its own: one block of 128^3 37.5 against 41.5 us, one
+// of 256^3 412 against 448, three of 101^3 (padded) 79.5 against 73.6, 64 of 40 x 24 x 33 169
+// against 39.
+bool copy_runs(const mhd_batch* c)
+{
+    return !c->fp32 && (c->runs.size() == 1 || c->ncell / c->runs.size() >= 1ULL << 21);
+}
+
 size_t state_bytes(const mhd_batch* c)
 {
     size_t t = 0;
@@ -757,6 +773,10 @@ mhd_status mhd_batch_create(int nblocks, const mhd_grid* grids, const mhd_physic
         }
         c->geo.push_back(q);
         desc[b] = BlockDesc{q, L.off[b], at};
+        if (b > 0 && L.off[b] - at == c->runs.back().off - c->runs.back().at)
+            c->runs.back().n += (unsigned long long)q.n;
+        else
+            c->runs.push_back({L.off[b], at, (unsigned long long)q.n});
         at += (unsigned long long)q.n;
         c->shape.push_back(default_shape(g.nx));
     }
@@ -832,6 +852,15 @@ mhd_status mhd_batch_set_state(mhd_batch* c, const double* src, int src_is_devic
 mhd_status mhd_batch_get_state(mhd_batch* c, double* dst, int dst_is_device)
 {
     if (!c || !dst) return MHD_E_INVAL;
+    if (copy_runs(c)) {
+        hipError_t e = hipSuccess;
+        for (size_t r = 0; r < c->runs.size() && e == hipSuccess; ++r)
+            e = hipMemcpyAsync(dst + 8 * c->runs[r].at, (const double*)c->reg[c->cur] + 8 * c->runs[r].off,
+                               (size_t)c->runs[r].n * 8 * sizeof(double),
+                               dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess && !dst_is_device) e = hipStreamSynchronize(c->stream);
+        return bdev(e);
+    }
     const bool direct = dst_is_device && in_place(dst, c->stream);
     double* d = direct ? dst : (double*)c->F;
     hipError_t e = launch_batch_store(c->d_blk, c->nb, state_grid(c), c->fp32, c->reg[c->cur], d, c->stream);

@@ -178,16 +178,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_store(const BlockDesc* __restr
     }
 }
 
-// dt[b] = scale * min of the `per` partials of block b; one wave each.
-__global__ __launch_bounds__(64) void k_batch_min(const double* __restrict__ partial, int per, double scale,
-                                                  double* __restrict__ dt)
-{
-    double r = INFINITY;
-    for (int q = threadIdx.x; q < per; q += 64) r = min_nan(r, partial[(long long)blockIdx.x * per + q]);
-    r = wave_min(r);
-    if (threadIdx.x == 0) dt[blockIdx.x] = scale * r;
-}
-
 // LOAD: the state also goes into the register reg on the way, FP32 forms rounded (192^3, 8
 // species: FP64 795 + 362 -> 784 us, FP32 355 + 581 -> 600 us against a copy or a
 // conversion of its own).
@@ -227,38 +217,41 @@ __global__ __launch_bounds__(kBlock) void k_cfl_dust(Geo g, DustParams p, const 
     if (threadIdx.x == 0) partial[blockIdx.x] = r;
 }
 
-// One workgroup of 16 waves, eight independent loads in flight per lane: bound by the
-// latency of its rounds of loads (27648 partials, the dust step at 192^3: 46 -> 9 us with
-// four waves and one load at a time before).
+// out[b] = scale * min of the m partials of block b, a workgroup of T lanes each, eight
+// independent loads in flight per lane: bound by the latency of its rounds of loads (one
+// block of 27648 partials, the dust step at 192^3: T = 1024, 46 -> 9 us with four waves and
+// one load at a time before).
 constexpr int kFinal = 1024;
-__global__ __launch_bounds__(kFinal) void k_min_final(const double* __restrict__ partial, long long m,
-                                                      double scale, double* __restrict__ out)
+template <int T>
+__global__ __launch_bounds__(T) void k_min_final(const double* __restrict__ partial, long long m, double scale,
+                                                 double* __restrict__ out)
 {
-    __shared__ double sm[kFinal / 64];
+    __shared__ double sm[T / 64];
+    partial += blockIdx.x * m;
     double r = INFINITY;
-    for (long long q0 = 0; q0 < m; q0 += 8 * kFinal) {
+    for (long long q0 = 0; q0 < m; q0 += 8 * T) {
         double v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const long long q = q0 + u * kFinal + (int)threadIdx.x;
+            const long long q = q0 + u * T + (int)threadIdx.x;
             v[u] = q < m ? partial[q] : INFINITY;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) r = min_nan(r, v[u]);
     }
     r = wave_min(r);
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = r;
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        r = wave_min(threadIdx.x < kFinal / 64 ? sm[threadIdx.x] : INFINITY);
-        if (threadIdx.x == 0) out[0] = scale * r;
+    if constexpr (T > 64) {
+        if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = r;
+        __syncthreads();
+        r = wave_min(threadIdx.x < T / 64 ? sm[threadIdx.x] : INFINITY);
     }
+    if (threadIdx.x == 0) out[blockIdx.x] = scale * r;
 }
 
 hipError_t launch_min_final(const double* partial, long long m, double scale, double* out,
                             hipStream_t s)
 {
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, m, scale, out);
+    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, m, scale, out);
     return hipGetLastError();
 }
 
@@ -267,7 +260,7 @@ hipError_t launch_cfl_mhd(const Geo& g, const MhdParams& p, const double* U, dou
 {
     const unsigned int nb = blocks_for(g.n);
     hipLaunchKernelGGL(k_cfl_mhd, dim3(nb), dim3(kBlock), 0, s, g, p, U, partial);
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt_out);
+    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt_out);
     return hipGetLastError();
 }
 
@@ -279,7 +272,7 @@ hipError_t launch_state_load(const Geo& g, const MhdParams& p, bool fp32, const 
         hipLaunchKernelGGL(k_state_load<float>, dim3(nb), dim3(kBlock), 0, s, g, p, src, (char*)reg, partial);
     else
         hipLaunchKernelGGL(k_state_load<double>, dim3(nb), dim3(kBlock), 0, s, g, p, src, (char*)reg, partial);
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt);
+    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt);
     return hipGetLastError();
 }
 
@@ -291,7 +284,11 @@ hipError_t launch_batch_load(const BlockDesc* blk, int nb, int per, const MhdPar
         hipLaunchKernelGGL(k_batch_load<float>, gr, bl, 0, s, blk, per, p, src, (char*)reg, partial);
     else
         hipLaunchKernelGGL(k_batch_load<double>, gr, bl, 0, s, blk, per, p, src, (char*)reg, partial);
-    hipLaunchKernelGGL(k_batch_min, dim3(nb), dim3(64), 0, s, partial, per, scale, dt);
+    // (one wave takes 512 partials in one round of loads)
+    if (per <= 512)
+        hipLaunchKernelGGL(k_min_final<64>, dim3(nb), dim3(64), 0, s, partial, (long long)per, scale, dt);
+    else
+        hipLaunchKernelGGL(k_min_final<kFinal>, dim3(nb), dim3(kFinal), 0, s, partial, (long long)per, scale, dt);
     return hipGetLastError();
 }
 
@@ -313,7 +310,7 @@ hipError_t launch_cfl_blocks(const Geo& pg, const MhdParams& p, const double* re
     const long long m = std::min<long long>(((long long)bx * by * bz * nb + kBlock - 1) / kBlock, 4096);
     hipLaunchKernelGGL(k_cfl_blocks, dim3((unsigned int)m), dim3(kBlock), 0, s, pg, p, reg, off, nb, ghost, bx, by, bz,
                        partial);
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, m, scale, dt_out);
+    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, m, scale, dt_out);
     return hipGetLastError();
 }
 
@@ -322,7 +319,7 @@ hipError_t launch_cfl_dust(const Geo& g, const DustParams& p, const double* U, d
 {
     const unsigned int nb = blocks_for(g.n);
     hipLaunchKernelGGL((k_cfl_dust<false, double>), dim3(nb), dim3(kBlock), 0, s, g, p, U, (double*)nullptr, partial);
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt_out);
+    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt_out);
     return hipGetLastError();
 }
 
@@ -334,7 +331,7 @@ hipError_t launch_dust_load(const Geo& g, const DustParams& p, bool fp32, const 
         hipLaunchKernelGGL((k_cfl_dust<true, float>), dim3(nb), dim3(kBlock), 0, s, g, p, src, (float*)reg, partial);
     else
         hipLaunchKernelGGL((k_cfl_dust<true, double>), dim3(nb), dim3(kBlock), 0, s, g, p, src, (double*)reg, partial);
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt);
+    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt);
     return hipGetLastError();
 }
 

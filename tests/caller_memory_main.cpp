@@ -138,13 +138,18 @@ int main(int argc, char** argv)
             say(who + "get", CALL(mhd_get_state)(c, caller, 1));
             CALL(mhd_destroy)(c);
         }
-        mhd_batch* b = nullptr;
-        const mhd_grid two[2] = {g, g};
-        check(CALL(mhd_batch_create)(2, two, &mhd, &sm, work, big, nullptr, &b), "batch");
-        trace.clear();
-        say(prec + "batch set", CALL(mhd_batch_set_state)(b, caller, 1));
-        say(prec + "batch get", CALL(mhd_batch_get_state)(b, caller, 1));
-        CALL(mhd_batch_destroy)(b);
+        // two blocks with padding between their registers, and two without
+        for (int dense = 0; dense < 2; ++dense) {
+            const mhd_grid small = {5, 4, 4, {1.0, 1.0, 1.0}};
+            const mhd_grid two[2] = {dense ? g : small, g};
+            const std::string who = prec + (dense ? "dense " : "batch ");
+            mhd_batch* b = nullptr;
+            check(CALL(mhd_batch_create)(2, two, &mhd, &sm, work, big, nullptr, &b), "batch");
+            trace.clear();
+            say(who + "set", CALL(mhd_batch_set_state)(b, caller, 1));
+            say(who + "get", CALL(mhd_batch_get_state)(b, caller, 1));
+            CALL(mhd_batch_destroy)(b);
+        }
         if (!fp32) {
             mhd_cnn* n = nullptr;
             check(CALL(mhd_cnn_create)(&g, &mhd, work, big, nullptr, &n), "network");
