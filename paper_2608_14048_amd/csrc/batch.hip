@@ -305,12 +305,6 @@ struct mhd_batch {
     int nb;
     std::vector<Geo> geo;
     std::vector<unsigned long long> off;
-    // blocks that lie one after the other in the registers as in a state: first cell in
-    // either, cells
-    struct Run {
-        unsigned long long off, at, n;
-    };
-    std::vector<Run> runs;
     unsigned long long ncell;  // padded total
     mhd_physics phys;
     mhd_scheme scheme;
@@ -698,15 +692,13 @@ int state_grid(const mhd_batch* c)
     return (int)std::max(1LL, std::min((8191LL + c->nb) / c->nb, cap));
 }
 
-// Whether a state of all blocks leaves the FP64 register by copies of its runs: on its own,
-// or with 2^21 cells and more to a run (134 MB).  A copy is 8 % faster than the kernel that
-// stores all blocks but costs a call of its own: one block of 128^3 37.5 against 41.5 us, one
-// of 256^3 412 against 448, three of 101^3 (padded) 79.5 against 73.6, 64 of 40 x 24 x 33 169
-// against 39.
-bool copy_runs(const mhd_batch* c)
-{
-    return !c->fp32 && (c->runs.size() == 1 || c->ncell / c->runs.size() >= 1ULL << 21);
-}
+// Whether the FP64 states leave by a copy per block: a single block, or blocks of a million
+// cells (64 MB) and more in the mean.  A copy of a large block is up to 8 % faster than the
+// kernel that stores all blocks but costs a call of its own (us, copies against the kernel):
+// one block of 128^3 37.5 and 41.5, one of 256^3 412 and 448, two of 16 x 16 x 4096 39.0 and
+// 40.2, three of 101^3 78.5 and 80.6; eight of 64 x 64 x 200 170 and 157, two of 64^3 12.0 and
+// 10.8, 64 of 40 x 24 x 33 169 and 39.
+bool copy_blocks(const mhd_batch* c) { return !c->fp32 && (c->nb == 1 || c->ncell / c->nb >= 1000000); }
 
 size_t state_bytes(const mhd_batch* c)
 {
@@ -773,10 +765,6 @@ mhd_status mhd_batch_create(int nblocks, const mhd_grid* grids, const mhd_physic
         }
         c->geo.push_back(q);
         desc[b] = BlockDesc{q, L.off[b], at};
-        if (b > 0 && L.off[b] - at == c->runs.back().off - c->runs.back().at)
-            c->runs.back().n += (unsigned long long)q.n;
-        else
-            c->runs.push_back({L.off[b], at, (unsigned long long)q.n});
         at += (unsigned long long)q.n;
         c->shape.push_back(default_shape(g.nx));
     }
@@ -852,12 +840,15 @@ mhd_status mhd_batch_set_state(mhd_batch* c, const double* src, int src_is_devic
 mhd_status mhd_batch_get_state(mhd_batch* c, double* dst, int dst_is_device)
 {
     if (!c || !dst) return MHD_E_INVAL;
-    if (copy_runs(c)) {
+    if (copy_blocks(c)) {
         hipError_t e = hipSuccess;
-        for (size_t r = 0; r < c->runs.size() && e == hipSuccess; ++r)
-            e = hipMemcpyAsync(dst + 8 * c->runs[r].at, (const double*)c->reg[c->cur] + 8 * c->runs[r].off,
-                               (size_t)c->runs[r].n * 8 * sizeof(double),
+        double* d = dst;
+        for (int b = 0; b < c->nb && e == hipSuccess; ++b) {
+            const size_t m = (size_t)c->geo[b].n * 8;
+            e = hipMemcpyAsync(d, (const double*)c->reg[c->cur] + c->off[b] * 8ULL, m * sizeof(double),
                                dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream);
+            d += m;
+        }
         if (e == hipSuccess && !dst_is_device) e = hipStreamSynchronize(c->stream);
         return bdev(e);
     }

@@ -138,13 +138,11 @@ int main(int argc, char** argv)
             say(who + "get", CALL(mhd_get_state)(c, caller, 1));
             CALL(mhd_destroy)(c);
         }
-        // two blocks with padding between their registers, and two without
-        for (int dense = 0; dense < 2; ++dense) {
-            const mhd_grid small = {5, 4, 4, {1.0, 1.0, 1.0}};
-            const mhd_grid two[2] = {dense ? g : small, g};
-            const std::string who = prec + (dense ? "dense " : "batch ");
+        for (int nb = 1; nb <= 2; ++nb) {
+            const mhd_grid both[2] = {g, g};
+            const std::string who = prec + (nb == 1 ? "block " : "batch ");
             mhd_batch* b = nullptr;
-            check(CALL(mhd_batch_create)(2, two, &mhd, &sm, work, big, nullptr, &b), "batch");
+            check(CALL(mhd_batch_create)(nb, both, &mhd, &sm, work, big, nullptr, &b), "batch");
             trace.clear();
             say(who + "set", CALL(mhd_batch_set_state)(b, caller, 1));
             say(who + "get", CALL(mhd_batch_get_state)(b, caller, 1));

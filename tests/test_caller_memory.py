@@ -36,14 +36,14 @@ def calls(tmp_path_factory):
     return run
 
 
-SETS = ["fp64 mhd set", "fp64 dust set", "fp64 batch set", "fp32 batch set", "fp64 dense set", "fp32 dense set",
+SETS = ["fp64 mhd set", "fp64 dust set", "fp64 batch set", "fp32 batch set", "fp64 block set", "fp32 block set",
         "fp64 closure coarse"]
-GETS = ["fp64 mhd get", "fp64 dust get", "fp64 batch get", "fp32 batch get", "fp64 dense get", "fp32 dense get"]
+GETS = ["fp64 mhd get", "fp64 dust get", "fp64 batch get", "fp32 batch get", "fp64 block get", "fp32 block get"]
 KINDS = ["other", "host", "managed", "unknown"]
 
 
 def _bytes(name):
-    return STATE + 5 * 4 * 4 * 8 * 8 if "batch" in name else STATE * (2 if "dense" in name else 1)
+    return STATE * (2 if "batch" in name else 1)
 
 
 @pytest.mark.parametrize("kind,offset", [("own", 4)] + [(k, 0) for k in KINDS])
@@ -67,9 +67,9 @@ def test_foreign_memory_goes_through_one_copy(calls, kind):
 
 def test_own_memory_is_read_in_place(calls):
     got = calls("own")
-    # (an FP64 register laid out as the state leaves by a copy wherever it goes)
-    assert got["fp64 dense get"] == f"[out {2 * STATE}]"
+    # (a single FP64 block leaves by a copy wherever it goes)
+    assert got["fp64 block get"] == f"[out {STATE}]"
     for name in SETS:
         assert "[" not in got[name] and "k" in got[name], (name, got[name])
-    for name in ("fp64 batch get", "fp32 batch get", "fp32 dense get", "fp32 mhd get", "fp32 dust get"):
+    for name in ("fp64 batch get", "fp32 batch get", "fp32 block get", "fp32 mhd get", "fp32 dust get"):
         assert got[name] == "k", (name, got[name])

@@ -1,7 +1,6 @@
-"""FP64 states of a batch out by copies of its runs (blocks that lie one after the other in
-the register as in a state) and by the storing kernel: one block, several without and with
-padding between them, and padded ones large enough to be copied one by one.  The time steps
-of blocks with more and fewer CFL partials than one wave takes in a round (512)."""
+"""FP64 states of a batch out by a copy per block (a single one, or large ones) and by the
+storing kernel, without and with padding between the blocks.  The time steps of blocks with
+more and fewer CFL partials than one wave takes in a round (512)."""
 import numpy as np
 import pytest
 
