@@ -218,10 +218,9 @@ __global__ __launch_bounds__(kBlock) void k_cfl_dust(Geo g, DustParams p, const 
 }
 
 // out[b] = scale * min of the m partials of block b, a workgroup of T lanes each, eight
-// independent loads in flight per lane: bound by the latency of its rounds of loads (one
-// block of 27648 partials, the dust step at 192^3: T = 1024, 46 -> 9 us with four waves and
-// one load at a time before).
-constexpr int kFinal = 1024;
+// independent loads in flight per lane: bound by the latency of its rounds of loads (27648
+// partials, the dust step at 192^3: T = 1024, 46 -> 9 us with four waves and one load at a
+// time before).
 template <int T>
 __global__ __launch_bounds__(T) void k_min_final(const double* __restrict__ partial, long long m, double scale,
                                                  double* __restrict__ out)
@@ -243,15 +242,28 @@ __global__ __launch_bounds__(T) void k_min_final(const double* __restrict__ part
     if constexpr (T > 64) {
         if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = r;
         __syncthreads();
+        if (threadIdx.x >= 64) return;
         r = wave_min(threadIdx.x < T / 64 ? sm[threadIdx.x] : INFINITY);
     }
     if (threadIdx.x == 0) out[blockIdx.x] = scale * r;
 }
 
+// nb blocks of m partials: as many lanes as one round of loads fills, within 64 and 1024 (up
+// to 512 partials 1.6 us with 64 lanes, 2.6 with 1024; four waves and one load at a time 1.7).
+static void min_final(const double* partial, long long m, int nb, double scale, double* out, hipStream_t s)
+{
+    if (m <= 8 * 64)
+        hipLaunchKernelGGL(k_min_final<64>, dim3(nb), dim3(64), 0, s, partial, m, scale, out);
+    else if (m <= 8 * 256)
+        hipLaunchKernelGGL(k_min_final<256>, dim3(nb), dim3(256), 0, s, partial, m, scale, out);
+    else
+        hipLaunchKernelGGL(k_min_final<1024>, dim3(nb), dim3(1024), 0, s, partial, m, scale, out);
+}
+
 hipError_t launch_min_final(const double* partial, long long m, double scale, double* out,
                             hipStream_t s)
 {
-    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, m, scale, out);
+    min_final(partial, m, 1, scale, out, s);
     return hipGetLastError();
 }
 
@@ -260,7 +272,7 @@ hipError_t launch_cfl_mhd(const Geo& g, const MhdParams& p, const double* U, dou
 {
     const unsigned int nb = blocks_for(g.n);
     hipLaunchKernelGGL(k_cfl_mhd, dim3(nb), dim3(kBlock), 0, s, g, p, U, partial);
-    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt_out);
+    min_final(partial, (long long)nb, 1, scale, dt_out, s);
     return hipGetLastError();
 }
 
@@ -272,7 +284,7 @@ hipError_t launch_state_load(const Geo& g, const MhdParams& p, bool fp32, const 
         hipLaunchKernelGGL(k_state_load<float>, dim3(nb), dim3(kBlock), 0, s, g, p, src, (char*)reg, partial);
     else
         hipLaunchKernelGGL(k_state_load<double>, dim3(nb), dim3(kBlock), 0, s, g, p, src, (char*)reg, partial);
-    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt);
+    min_final(partial, (long long)nb, 1, scale, dt, s);
     return hipGetLastError();
 }
 
@@ -284,11 +296,7 @@ hipError_t launch_batch_load(const BlockDesc* blk, int nb, int per, const MhdPar
         hipLaunchKernelGGL(k_batch_load<float>, gr, bl, 0, s, blk, per, p, src, (char*)reg, partial);
     else
         hipLaunchKernelGGL(k_batch_load<double>, gr, bl, 0, s, blk, per, p, src, (char*)reg, partial);
-    // (one wave takes 512 partials in one round of loads)
-    if (per <= 512)
-        hipLaunchKernelGGL(k_min_final<64>, dim3(nb), dim3(64), 0, s, partial, (long long)per, scale, dt);
-    else
-        hipLaunchKernelGGL(k_min_final<kFinal>, dim3(nb), dim3(kFinal), 0, s, partial, (long long)per, scale, dt);
+    min_final(partial, per, nb, scale, dt, s);
     return hipGetLastError();
 }
 
@@ -310,7 +318,7 @@ hipError_t launch_cfl_blocks(const Geo& pg, const MhdParams& p, const double* re
     const long long m = std::min<long long>(((long long)bx * by * bz * nb + kBlock - 1) / kBlock, 4096);
     hipLaunchKernelGGL(k_cfl_blocks, dim3((unsigned int)m), dim3(kBlock), 0, s, pg, p, reg, off, nb, ghost, bx, by, bz,
                        partial);
-    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, m, scale, dt_out);
+    min_final(partial, m, 1, scale, dt_out, s);
     return hipGetLastError();
 }
 
@@ -319,7 +327,7 @@ hipError_t launch_cfl_dust(const Geo& g, const DustParams& p, const double* U, d
 {
     const unsigned int nb = blocks_for(g.n);
     hipLaunchKernelGGL((k_cfl_dust<false, double>), dim3(nb), dim3(kBlock), 0, s, g, p, U, (double*)nullptr, partial);
-    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt_out);
+    min_final(partial, (long long)nb, 1, scale, dt_out, s);
     return hipGetLastError();
 }
 
@@ -331,7 +339,7 @@ hipError_t launch_dust_load(const Geo& g, const DustParams& p, bool fp32, const 
         hipLaunchKernelGGL((k_cfl_dust<true, float>), dim3(nb), dim3(kBlock), 0, s, g, p, src, (float*)reg, partial);
     else
         hipLaunchKernelGGL((k_cfl_dust<true, double>), dim3(nb), dim3(kBlock), 0, s, g, p, src, (double*)reg, partial);
-    hipLaunchKernelGGL(k_min_final<kFinal>, dim3(1), dim3(kFinal), 0, s, partial, (long long)nb, scale, dt);
+    min_final(partial, (long long)nb, 1, scale, dt, s);
     return hipGetLastError();
 }
 
