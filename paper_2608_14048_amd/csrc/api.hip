@@ -433,7 +433,8 @@ mhd_status mhd_create(const mhd_grid* grid, const mhd_physics* phys, const mhd_s
     c->geo = make_geo(grid);
     c->fp32 = scheme->prec == MHD_PREC_FP32_BULK;
     c->fg = fused_grid(c->geo, choose_kz(grid), c->fp32);
-    c->dg = dust_grid(c->geo, 1 + (phys->eos == MHD_EOS_ADIABATIC_MHD ? 0 : phys->ndust));
+    c->dg = dust_grid(c->geo, 1 + (phys->eos == MHD_EOS_ADIABATIC_MHD ? 0 : phys->ndust), scheme->recon,
+                      c->fp32);
     c->cfl_scale = make_params(phys, scheme, &c->mp, &c->dp);
 
     char* base = (char*)device_workspace;

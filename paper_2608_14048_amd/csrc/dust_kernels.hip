@@ -204,7 +204,7 @@ template <int RECON, class R, int NR>
 struct PassLds {
     static constexpr int LX = DTX + 2 * Halo<RECON>::H;
     R row[NR][4][LX];  // primitives of the wave's rows with their x halo
-    R edge[NR][2][4];  // high-side state of column x0 - 1, flux through face x0 + 63 1/2
+    R edge[NR][2][4];  // (not SOLO) high-side state of column x0 - 1, flux through face x0 + 63 1/2
 };
 
 // One wave's tile of fluid s (GAS: the gas, else a dust species; a template argument so
@@ -215,7 +215,10 @@ struct PassLds {
 // double-buffered LDS and solved both faces of every cell in x and y (five Riemann
 // problems and seven slopes per variable and cell; here four and five).  Four rows need
 // more registers than two waves per SIMD leave (FP64 spills: 3.7 ms; FP32 0.96 ms).
-template <int RECON, int STAGE, class R, int NR, bool GAS>
+// SOLO (a single row): every lane solves both faces of its cell along x instead of the edge
+// faces' own pass.  As many instructions, without the wait for a second exchange, but more
+// registers (FP64 PLM 184 against 164, two waves per SIMD against three).
+template <int RECON, int STAGE, class R, int NR, bool GAS, bool SOLO>
 __device__ __forceinline__ void fluid_tile(const Geo& g, const DustParams& p, const PassArgs<R>& a, int s, int x0,
                                            int y0, int k0, int k1, PassLds<RECON, R, NR>& lds)
 {
@@ -318,7 +321,7 @@ __device__ __forceinline__ void fluid_tile(const Geo& g, const DustParams& p, co
         if (more && lane < NX) load_raw(pb + plane + xoff, xraw);
         wave_sync();
         // ---- the edge faces of all rows in one pass: lane 2 r + e the face at x0 + 64 e of row r
-        if (lane < 2 * NR) {
+        if (!SOLO && lane < 2 * NR) {
             const int r = lane >> 1, e = lane & 1;
             R lo[4], hi[4], fx[4], dum;
 #pragma unroll
@@ -336,7 +339,7 @@ __device__ __forceinline__ void fluid_tile(const Geo& g, const DustParams& p, co
 #pragma unroll
             for (int v = 0; v < 4; ++v) lds.edge[r][e][v] = e ? fx[v] : hi[v];
         }
-        wave_sync();
+        if constexpr (!SOLO) wave_sync();
 
         R hv[2 * H][4];
 #pragma unroll
@@ -368,7 +371,25 @@ __device__ __forceinline__ void fluid_tile(const Geo& g, const DustParams& p, co
             }
             // acc = ((fx + fy) + fz): flux differences over the spacings, direction by direction
             R acc[4];
-            {
+            if constexpr (SOLO) {
+                R lo[4], hi[4], ot[4], fl[4], dum;  // own states, the one beside
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const R* q = &lds.row[r][v][lane + H];
+                    const R a0 = zl[r][v].here();
+                    cell_states<RECON, R>(q[-1], a0, q[1], lo[v], hi[v]);
+                    cell_states<RECON, R>(q[-H], q[-1], a0, dum, ot[v]);
+                }
+                face_flux<0, GAS>(cs, ot, lo, fl);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const R* q = &lds.row[r][v][lane + H];
+                    cell_states<RECON, R>(zl[r][v].here(), q[1], q[H], ot[v], dum);
+                }
+                face_flux<0, GAS>(cs, hi, ot, lo);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[v] = lo[v] - fl[v];
+            } else {
                 R lo[4], hi[4], L[4], fl[4], ed[4];
                 const R* e = &lds.edge[r][lane == 63][0];
 #pragma unroll
@@ -439,7 +460,7 @@ __device__ __forceinline__ void fluid_tile(const Geo& g, const DustParams& p, co
     }
 }
 
-template <int RECON, int STAGE, class R, int NR>
+template <int RECON, int STAGE, class R, int NR, bool SOLO>
 __global__ __launch_bounds__(64 * DWAVES) __attribute__((amdgpu_waves_per_eu(2))) void k_fluid_pass(
     Geo g, DustParams p, PassArgs<R> a, int kz, unsigned int ntx, unsigned int nty, unsigned int ntiles,
     unsigned int nitems, unsigned int nblk)
@@ -455,9 +476,205 @@ __global__ __launch_bounds__(64 * DWAVES) __attribute__((amdgpu_waves_per_eu(2))
     const int k0 = __builtin_amdgcn_readfirstlane((int)(t / (ntx * nty)) * kz);
     const int k1 = min(k0 + kz, g.nz);
     if (s == 0)
-        fluid_tile<RECON, STAGE, R, NR, true>(g, p, a, s, x0, y0, k0, k1, lds[wv]);
+        fluid_tile<RECON, STAGE, R, NR, true, SOLO>(g, p, a, s, x0, y0, k0, k1, lds[wv]);
     else
-        fluid_tile<RECON, STAGE, R, NR, false>(g, p, a, s, x0, y0, k0, k1, lds[wv]);
+        fluid_tile<RECON, STAGE, R, NR, false, SOLO>(g, p, a, s, x0, y0, k0, k1, lds[wv]);
+}
+
+// What a pass takes of its arguments, in its own real.
+template <class R>
+struct PassConst {
+    R cs, rho_floor, dust_floor, gx[3], h, cu, c1, idx[3];
+    __device__ PassConst(const Geo& g, const DustParams& p, const PassArgs<R>& a)
+        : cs(R(p.cs)), rho_floor(R(p.rho_floor)), dust_floor(R(p.dust_floor)),
+          gx{R(p.gacc[0]), R(p.gacc[1]), R(p.gacc[2])}, h(R(a.h)), cu(R(a.cu)), c1(R(a.c1)),
+          idx{R(g.inv_dx[0]), R(g.inv_dx[1]), R(g.inv_dx[2])}
+    {
+    }
+};
+
+// Primitives from the raw state: the gas density is floored; a dust species below its floor
+// reads as the floor at rest.
+template <bool GAS, class R>
+__device__ __forceinline__ void prim_of(const PassConst<R>& q, const R raw[4], R w[4])
+{
+#pragma clang fp contract(off)
+    const bool rest = !GAS && raw[0] < q.dust_floor;
+    R d = raw[0];
+    if (GAS && d < q.rho_floor) d = q.rho_floor;
+    const R id = rcp(d);
+    w[0] = rest ? q.dust_floor : d;
+    w[1] = rest ? R(0) : raw[1] * id;
+    w[2] = rest ? R(0) : raw[2] * id;
+    w[3] = rest ? R(0) : raw[3] * id;
+}
+
+// The stage's explicit part of cell c from its raw state own, the step's input (stage 2: ub)
+// and the flux divergence acc.  The input passes the dust floor reset (a species below its
+// floor becomes the floor at rest) where it enters the combination, in both stages.
+template <int STAGE, bool GAS, class R>
+__device__ __forceinline__ void stage_store(const PassConst<R>& q, R own[4], R ub[4], const R acc[4], R* const o[4],
+                                            unsigned int c)
+{
+#pragma clang fp contract(off)
+    R* uin = STAGE == 1 ? own : ub;
+    if (!GAS && uin[0] < q.dust_floor) {
+        uin[0] = q.dust_floor;
+        uin[1] = uin[2] = uin[3] = R(0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        R L = -acc[v];
+        // the gas acceleration acts on the raw gas density
+        if (GAS && v > 0) L = fma_r(own[0], q.gx[v - 1], L);
+        R X;
+        if constexpr (STAGE == 1)
+            X = fma_r(q.h, L, own[v]);
+        else
+            X = fma_r(q.h, L, fma_r(q.cu, ub[v], q.c1 * own[v]));
+        st(o[v], c, X);
+    }
+}
+
+// The donor cell in FP64 on larger grids: a workgroup of four waves on 64 x 4 columns of one
+// fluid, a row each, that stage the primitives of a plane with its x/y halo in LDS (double
+// buffered: the loads of plane k + 1 go out before plane k is computed).  Without slopes the
+// passes are bound by their loads, and a halo row is read here once per four rows without
+// the registers of four; every cell solves both of its x and y faces (no exchange).  A stage
+// of 148 x 46 x 88 with 9 species 463 us a step against 480 to 490 with independent waves of
+// 1 or 2 rows in chunks of any length, 120 x 174 x 210 with 4 1621 against 1675, 100^3 with 4
+// 388 against 396; with 4 rows a wave 468, 1648, 392 at the best chunk, up to 8 % more at the
+// next.  FP32 gains from independent waves (128^3 with 8 694 against 656).
+constexpr int DTY = 4;
+
+template <int STAGE, class R, bool GAS>
+__device__ __forceinline__ void donor_block(const Geo& g, const DustParams& p, const PassArgs<R>& a, int s, int x0,
+                                            int y0, int k0, int k1, R (&sw)[2][4][DTY + 2][DTX + 2])
+{
+    // every rounding as in fluid_tile: the two give the same bits
+#pragma clang fp contract(off)
+    constexpr int LX = DTX + 2, LY = DTY + 2, NT = DTX * DTY, NI = (LX * LY + NT - 1) / NT;
+    const int lane = (int)threadIdx.x & 63, row = (int)threadIdx.x >> 6;
+    const int i = x0 + lane, j = y0 + row;
+    const bool live = i < g.nx && j < g.ny;
+    const long long n = g.n;
+    const unsigned int plane = (unsigned int)g.nx * (unsigned int)g.ny;
+    const unsigned int col = live ? (unsigned int)j * (unsigned int)g.nx + (unsigned int)i : 0u;
+    const R *f[4], *b[4];
+    R* o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f[q] = a.src + (4LL * s + q) * n;
+        b[q] = a.base + (4LL * s + q) * n;
+        o[q] = a.out + (4LL * s + q) * n;
+    }
+    const PassConst<R> pc(g, p, a);
+    auto load_raw = [&](unsigned int c, R raw[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) raw[q] = ld(f[q], c);
+    };
+    // this thread's staging items of a plane (tile and halo without corners; a thread
+    // without one loads cell 0 of the plane)
+    unsigned int soff[NI];
+    int at[NI];
+#pragma unroll
+    for (int m = 0; m < NI; ++m) {
+        const int q = (int)threadIdx.x + m * NT, sr = q / LX, sc = q - sr * LX;
+        const bool xh = sc < 1 || sc > DTX, yh = sr < 1 || sr > DTY;
+        const bool has = q < LX * LY && !(xh && yh);
+        at[m] = has ? q : -1;
+        soff[m] = has ? (unsigned int)wrap_any(y0 + sr - 1, g.ny) * (unsigned int)g.nx +
+                            (unsigned int)wrap_any(x0 + sc - 1, g.nx)
+                      : 0u;
+    }
+    R raw[NI][4];
+    auto fetch_plane = [&](int kk) {
+#pragma unroll
+        for (int m = 0; m < NI; ++m) load_raw((unsigned int)kk * plane + soff[m], raw[m]);
+    };
+    auto store_plane = [&](int buf) {
+#pragma unroll
+        for (int m = 0; m < NI; ++m)
+            if (at[m] >= 0) {
+                R w[4];
+                prim_of<GAS>(pc, raw[m], w);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) (&sw[buf][v][0][0])[at[m]] = w[v];
+            }
+    };
+    // the z faces of the own column: primitives below, flux through the low face
+    R zb[4], fz[4], zraw[4];
+    {
+        R r4[4], w[4];
+        load_raw((unsigned int)wrap_any(k0 - 1, g.nz) * plane + col, r4);
+        load_raw((unsigned int)k0 * plane + col, zraw);
+        prim_of<GAS>(pc, r4, w);
+        prim_of<GAS>(pc, zraw, zb);
+        face_flux<2, GAS>(pc.cs, w, zb, fz);
+    }
+    load_raw((unsigned int)wrap_any(k0 + 1, g.nz) * plane + col, zraw);
+    fetch_plane(k0);
+    store_plane(k0 & 1);
+    __syncthreads();
+    for (int k = k0; k < k1; ++k) {
+        const bool more = k + 1 < k1;
+        if (more) fetch_plane(k + 1);
+        const unsigned int c = (unsigned int)k * plane + col;
+        R own[4], ub[4], zw[4];
+        load_raw(c, own);
+        if constexpr (STAGE == 2) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) ub[v] = ld(b[v], c);
+        }
+        prim_of<GAS>(pc, zraw, zw);
+        if (more) load_raw((unsigned int)wrap_any(k + 2, g.nz) * plane + col, zraw);
+        R acc[4], L[4], C[4], Rr[4], fl[4], fh[4];
+        const R(&w)[4][LY][LX] = sw[k & 1];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            L[v] = w[v][row + 1][lane];
+            C[v] = w[v][row + 1][lane + 1];
+            Rr[v] = w[v][row + 1][lane + 2];
+        }
+        face_flux<0, GAS>(pc.cs, L, C, fl);
+        face_flux<0, GAS>(pc.cs, C, Rr, fh);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            acc[v] = fh[v] - fl[v];
+            L[v] = w[v][row][lane + 1];
+            Rr[v] = w[v][row + 2][lane + 1];
+        }
+        face_flux<1, GAS>(pc.cs, L, C, fl);
+        face_flux<1, GAS>(pc.cs, C, Rr, fh);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = fma_r(acc[v], pc.idx[0], (fh[v] - fl[v]) * pc.idx[1]);
+        face_flux<2, GAS>(pc.cs, zb, zw, fh);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            acc[v] = fma_r(fh[v] - fz[v], pc.idx[2], acc[v]);
+            fz[v] = fh[v];
+            zb[v] = zw[v];
+        }
+        if (live) stage_store<STAGE, GAS>(pc, own, ub, acc, o, c);
+        if (more) store_plane((k + 1) & 1);
+        __syncthreads();
+    }
+}
+
+template <int STAGE, class R>
+__global__ __launch_bounds__(DTX* DTY) void k_donor_pass(Geo g, DustParams p, PassArgs<R> a, int kz, unsigned int ntx,
+                                                         unsigned int nty, unsigned int ntiles, unsigned int nblk)
+{
+    __shared__ R sw[2][4][DTY + 2][DTX + 2];  // primitives of plane k, and of k + 1 being staged
+    const unsigned int item = xcd_item(blockIdx.x, nblk);
+    const int s = (int)(item / ntiles);  // fluid: 0 gas, 1.. dust
+    const unsigned int t = item - (unsigned int)s * ntiles;
+    const int x0 = (int)(t % ntx) * DTX, y0 = (int)((t / ntx) % nty) * DTY, k0 = (int)(t / (ntx * nty)) * kz;
+    const int k1 = min(k0 + kz, g.nz);
+    if (s == 0)
+        donor_block<STAGE, R, true>(g, p, a, s, x0, y0, k0, k1, sw);
+    else
+        donor_block<STAGE, R, false>(g, p, a, s, x0, y0, k0, k1, sw);
 }
 
 // ----------------------------------------------------------------------------------
@@ -622,32 +839,45 @@ static hipError_t drag_dispatch(const Geo& g, const DustParams& p, const DragCoe
 
 // ----------------------------------------------------------------------------------
 
-// Rows per wave and planes per chunk.  Two rows share their y faces and halo rows, and a
-// chunk primes its z pipeline once, but a small grid needs the waves: two rows where
-// chunks of four planes still give 4096 waves (two rounds of what the GPU holds at two per
-// SIMD), else one row and the chunk of 2 to 8 planes that takes the fewest plane times in
-// rounds of 4096 waves, a chunk costing about 1.5 planes beside its own (70 grids of up to
-// 4e6 cells x fluids: 1.4 % faster in the mean than two planes always, in both precisions,
-// where that lost up to 3.5 % in FP32 to tiles of whole workgroups); beyond, about 16384 waves, whose last
-// round costs little.  FP64 stage 1, us, one row and 2 planes / two rows and 4
-// planes at least: 24^3 with 2 species 13 / 25, 40^3 with 4 29 / 28, 64^3 with 8 89 / 80,
-// 128^3 with 8 553 / 531; 192^3 with 8 by waves 8192 / 16384 / 32768: 1722 / 1670 / 1700.
-DustGrid dust_grid(const Geo& g, int nfluids)
+// Tile and planes per chunk.  Two rows share their y faces and halo rows, and a chunk primes
+// its z pipeline once, but a small grid needs the waves: two rows where chunks of four planes
+// still give 2048 waves (PLM: a round of what the GPU holds at two per SIMD; 48^3 with 8
+// species FP64 135 -> 124 us a step, FP32 77 -> 72) or 4096 (FP32 donor cell), beyond about
+// 16384 waves, whose last round costs little (192^3 with 8 by waves 8192 / 16384 / 32768: 1722
+// / 1670 / 1700 us a stage).  Else one row and the chunk of 2 to 8 planes that takes the
+// fewest plane times in rounds of 4096 waves, a chunk costing about 1.5 planes beside its own
+// (two rounds of 2048: with one as the unit 70 grids of up to 4e6 cells x fluids take as long
+// in FP64 and 1 % longer in FP32).  FP64 stage 1, us, one row and 2 planes / two rows and 4 at
+// least: 24^3 with 2 species 13 / 25, 40^3 with 4 29 / 28, 64^3 with 8 89 / 80.
+// The donor cell in FP64 has one row a wave, in chunks of four planes beyond 8192 waves (64^3
+// with 16 species 284 -> 274 us a step, 256 x 256 x 4 with 8 163 -> 152), up to where two
+// would give 12288 waves, and from there blocks of four, about 4096 of them.
+// A single row whose waves all run at once (two per SIMD) is solo: 4096 x 1 x 1 with 2 species
+// FP64 7.7 -> 7.0 us a stage; with more waves its registers cost more (48 x 30 x 102 with 1
+// 57.9 -> 58.8 us a step).
+DustGrid dust_grid(const Geo& g, int nfluids, int recon, bool fp32)
 {
     DustGrid d;
     d.ntx = (unsigned int)((g.nx + DTX - 1) / DTX);
     const long long cols = (long long)d.ntx * nfluids;
-    d.rows = cols * ((g.ny + 1) / 2) * ((g.nz + 3) / 4) >= 4096 ? 2 : 1;
+    const bool donor = recon == 0 && !fp32;
+    const long long pairs = cols * ((g.ny + 1) / 2) * ((g.nz + 3) / 4);
+    const bool many = pairs >= (recon != 0 ? 2048 : fp32 ? 4096 : 12288);
+    d.block = many && donor;
+    d.rows = d.block ? DTY : many ? 2 : 1;
     d.nty = (unsigned int)((g.ny + d.rows - 1) / d.rows);
     const long long tiles = cols * d.nty;
-    const long long want = (16384 + tiles - 1) / tiles;
-    int kz = (int)((g.nz + want - 1) / want);
-    if (kz < 4) kz = 4;
-    if (d.rows == 1) {
+    auto chunks = [&](int q) { return (long long)(g.nz + q - 1) / q; };
+    int kz = 4;
+    if (many) {
+        const long long want = ((d.block ? 4096 : 16384) + tiles - 1) / tiles;
+        const int least = d.block ? 8 : 4;
+        kz = (int)((g.nz + want - 1) / want);
+        if (kz < least) kz = least;
+    } else if (!donor || tiles * chunks(4) <= 8192) {
         long long best = -1;
         for (int q = 2; q <= 8; ++q) {
-            const long long waves = tiles * ((g.nz + q - 1) / q);
-            const long long cost = (waves + 4095) / 4096 * (2 * q + 3);
+            const long long cost = (tiles * chunks(q) + 4095) / 4096 * (2 * q + 3);
             if (best < 0 || cost < best) {
                 best = cost;
                 kz = q;
@@ -659,20 +889,21 @@ DustGrid dust_grid(const Geo& g, int nfluids)
     d.ntz = (unsigned int)((g.nz + kz - 1) / kz);
     d.ntiles = d.ntx * d.nty * d.ntz;
     d.nitems = d.ntiles * (unsigned int)nfluids;
-    d.nblk = (d.nitems + DWAVES - 1) / DWAVES;
+    d.solo = d.rows == 1 && d.nitems <= 2048;
+    d.nblk = d.block ? d.nitems : (d.nitems + DWAVES - 1) / DWAVES;
     return d;
 }
 
-template <int RECON, class R, int NR>
+template <int RECON, class R, int NR, bool SOLO>
 static hipError_t pass_rows(const Geo& g, const DustParams& p, const DustGrid& d, int stage, const PassArgs<R>& a,
                             hipStream_t s)
 {
     const dim3 gr(d.nblk), bl(64 * DWAVES);
     if (stage == 1)
-        hipLaunchKernelGGL((k_fluid_pass<RECON, 1, R, NR>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles,
+        hipLaunchKernelGGL((k_fluid_pass<RECON, 1, R, NR, SOLO>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles,
                            d.nitems, d.nblk);
     else
-        hipLaunchKernelGGL((k_fluid_pass<RECON, 2, R, NR>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles,
+        hipLaunchKernelGGL((k_fluid_pass<RECON, 2, R, NR, SOLO>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles,
                            d.nitems, d.nblk);
     return hipGetLastError();
 }
@@ -681,8 +912,20 @@ template <int RECON, class R>
 static hipError_t pass(const Geo& g, const DustParams& p, const DustGrid& d, int stage, const PassArgs<R>& a,
                        hipStream_t s)
 {
-    if (d.rows == 2) return pass_rows<RECON, R, 2>(g, p, d, stage, a, s);
-    return pass_rows<RECON, R, 1>(g, p, d, stage, a, s);
+    if constexpr (RECON == 0 && sizeof(R) == 8) {
+        if (d.block) {
+            const dim3 gr(d.nblk), bl(DTX * DTY);
+            if (stage == 1)
+                hipLaunchKernelGGL((k_donor_pass<1, R>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles, d.nblk);
+            else
+                hipLaunchKernelGGL((k_donor_pass<2, R>), gr, bl, 0, s, g, p, a, d.kz, d.ntx, d.nty, d.ntiles, d.nblk);
+            return hipGetLastError();
+        }
+    } else if (d.rows == 2) {
+        return pass_rows<RECON, R, 2, false>(g, p, d, stage, a, s);
+    }
+    if (d.solo) return pass_rows<RECON, R, 1, true>(g, p, d, stage, a, s);
+    return pass_rows<RECON, R, 1, false>(g, p, d, stage, a, s);
 }
 
 template <class R>

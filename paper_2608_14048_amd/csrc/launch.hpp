@@ -139,9 +139,11 @@ hipError_t launch_diag(const Geo& g, int mhd, int ndust, const double* U, double
 // Tiling of the fluid passes: one wave per (fluid, 64 x rows tile, chunk of kz planes).
 struct DustGrid {
     int kz, rows;
+    bool block;  // tiles of a workgroup (donor cell, FP64), else of a wave
+    bool solo;   // waves of a single row that solve both x faces of their cells
     unsigned int ntx, nty, ntz, ntiles, nitems, nblk;
 };
-DustGrid dust_grid(const Geo& g, int nfluids);
+DustGrid dust_grid(const Geo& g, int nfluids, int recon, bool fp32);
 // Explicit parts: stage 1 writes X = u + lam dt L(u) into U1; stage 2 writes
 // X = cu u + c1 U1 + (1 - delta) dt L(U1) over u in place.  fp32: the registers hold
 // FP32 fields (explicit part in FP32, drag solve in FP64).
