@@ -199,7 +199,9 @@ mhd_status mhd_diagnostics(mhd_ctx* ctx, double* out, int n);
  * records a pair of HIP events on the context's stream around each kernel launch,
  * for up to `capacity` launches between reads (later launches are not recorded);
  * capacity 0 turns timing off and releases the events.  Host-side events only: no
- * device memory is allocated. */
+ * device memory is allocated.  The class `cfl` is the time step of a state that goes in
+ * (or changes in place); a state read where it lies on the device is loaded in the same
+ * launch, which then counts in full. */
 mhd_status mhd_timing_enable(mhd_ctx* ctx, int capacity);
 
 /* Synchronise the stream, then write for each kernel class q < nslot the summed

@@ -470,7 +470,7 @@ mhd_status build_items(mhd_batch* c, const std::vector<char>& include)
         if (!include[b]) continue;
         const Geo& g = c->geo[b];
         const int s = c->shape[b];
-                // the cells whose face fields are advanced, and one more on every side, whose
+        // the cells whose face fields are advanced, and one more on every side, whose
         // fluxes and face values the edges around them take: all of a block on its own, the
         // interior of a coupled one (the exchange fills every ghost cell after the stage).
         // 8 blocks of 128^3 and 3 ghost layers: the CT kernels 936 + 1052 -> 680 + 761 us, the

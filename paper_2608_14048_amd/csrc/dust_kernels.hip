@@ -26,9 +26,12 @@
 //                 flux to the lane on its left; the two faces at the tile's edge of all
 //                 rows are solved together in one more pass.  A face is solved once per
 //                 direction within a tile (x: 1 + 1/rows per cell, y: 1 + 1/rows, z: 1)
-//                 and a cell's slope once, and each stage's explicit part is written:
+//                 and a cell's slope once (x twice on small grids, where a lane solves
+//                 both faces of its cell), and each stage's explicit part is written:
 //                   stage 1: X = u + h L(u);  stage 2: X = cu u + c1 U1 + cf L(U1).
 //                 Densities are final after this pass (drag moves only momentum).
+//   k_donor_pass  the same for the donor cell in FP64 on larger grids, a workgroup per
+//                 64 x 4 columns of a fluid.
 //   k_drag        pointwise: adds the stage-1 drag rates (stage 2), solves S_h for the
 //                 momenta in place and, after stage 2, reduces the CFL step of the new
 //                 state (one partial per workgroup).
@@ -112,7 +115,7 @@ __device__ __forceinline__ void face_flux(R cs, const R L[4], const R Rs[4], R o
 }  // namespace
 
 // ----------------------------------------------------------------------------------
-// explicit part of a stage, one fluid per workgroup
+// explicit part of a stage, one fluid per wave (or per workgroup, donor cell in FP64)
 // ----------------------------------------------------------------------------------
 
 template <class R>

@@ -66,8 +66,6 @@ __device__ __forceinline__ double min_r(double a, double b) { return fmin(a, b);
 __device__ __forceinline__ float min_r(float a, float b) { return fminf(a, b); }
 __device__ __forceinline__ double max_r(double a, double b) { return fmax(a, b); }
 __device__ __forceinline__ float max_r(float a, float b) { return fmaxf(a, b); }
-__device__ __forceinline__ double copysign_r(double a, double b) { return __builtin_copysign(a, b); }
-__device__ __forceinline__ float copysign_r(float a, float b) { return __builtin_copysignf(a, b); }
 // a * b + c with one rounding (written out where a formula wants it, so that the
 // rounding of a helper does not depend on where the compiler inlines it)
 __device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
@@ -428,9 +426,10 @@ __device__ __forceinline__ void riemann_hlld(const Prim7<R>& L, const Prim7<R>& 
 
     // The star states are built in every lane (lanes of one wave rarely all agree on a
     // supersonic face, and one straight block schedules better than a divergent one); what
-    // a region does not need is left out of its flux below, not multiplied by zero.  The
-    // divergent form kept 40 register moves per face for the values its branches merge
-    // (FP64 PPM corrector at 256^3: 2.53 -> 2.36 ms per launch).
+    // a region does not need is left out of its flux below, not multiplied by zero (so an
+    // infinite value stays infinite there).  The divergent form kept 40 register moves per
+    // face for the values its branches merge (FP64 PPM corrector at 256^3: 2.51 -> 2.44 ms
+    // per launch).
     const bool sup = sl > R(0) || sr < R(0);
     const R ml = L.d * (sl - L.vn), mr = Rt.d * (sr - Rt.vn);  // mass fluxes into the fan
     const R iden = rcp(mr - ml);
