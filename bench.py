@@ -68,13 +68,13 @@ KERNEL_ALGO = {
     "cfl": {"bytes": 8 * 8, "flops": 72},
 }
 
-# FP32-bulk form: a state is 7 FP32 fields + FP64 E = 36 B (cell fields: 3 x 4 + 8 = 20
+# FP32-bulk form: a state is 7 FP32 fields + FP64 E = 36 B (cell fields: 4 x 4 + 8 = 24
 # B; face fields 12 B), a face or cell-E field 4 B; the flops are those of the FP64
 # table, in FP32 (E's update in FP64)
 KERNEL_ALGO_FP32 = {
-    "mhd_flux_update_corrector": {"bytes": 36 + 20 + 20 + 9 * 4 + 1, "flops": 1741, "stage": "corrector"},
-    "mhd_flux_update_predictor": {"bytes": 36 + 20 + 9 * 4 + 1, "flops": 1195, "stage": "predictor"},
-    "mhd_ct_corrector": {"bytes": 9 * 4 + 1 + 12 + 12 + 20, "flops": 152, "stage": "corrector"},
+    "mhd_flux_update_corrector": {"bytes": 36 + 24 + 24 + 9 * 4 + 1, "flops": 1741, "stage": "corrector"},
+    "mhd_flux_update_predictor": {"bytes": 36 + 24 + 9 * 4 + 1, "flops": 1195, "stage": "predictor"},
+    "mhd_ct_corrector": {"bytes": 9 * 4 + 1 + 12 + 12 + 24, "flops": 152, "stage": "corrector"},
     "mhd_ct_predictor": {"bytes": 9 * 4 + 1 + 12 + 12, "flops": 80, "stage": "predictor"},
     "cfl": {"bytes": 36, "flops": 72},
 }
