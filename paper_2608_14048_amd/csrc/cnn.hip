@@ -17,10 +17,11 @@
 // v_mfma_f32_16x16x16_bf16 for the first layer's 16 (8 padded).  Activations are
 // stored channel-last ([voxel][channel], channels padded to 16 or 32) so that one
 // lane's K values are one 8- or 16-byte read.  Persistent workgroups hold the weight
-// fragments of all 27 taps in registers and take 16 x 4 x 8 voxel blocks through LDS
-// (k_conv).  The backward data pass is the same kernel on reflected, transposed weights
-// with the ReLU mask of the layer below; the weight and bias gradients are a GEMM over
-// voxels per tap (MFMA with K along voxels, k_grad) with one partial per workgroup.
+// fragments of all 27 taps in registers and take 16 x 4 x 8 voxel blocks (flat ones on
+// grids of few planes or rows) through LDS (k_conv).  The backward data pass is the
+// same kernel on reflected, transposed weights with the ReLU mask of the layer below;
+// the weight and bias gradients are a GEMM over voxels per tap (MFMA with K along
+// voxels, k_grad) with one partial per workgroup.
 // Master weights and Adam moments are FP32; the BF16 copies are refreshed after each
 // update.
 //

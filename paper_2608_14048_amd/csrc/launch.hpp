@@ -136,7 +136,8 @@ hipError_t launch_diag(const Geo& g, int mhd, int ndust, const double* U, double
                        double* out, hipStream_t s);
 
 // ---- isothermal gas + dust (IMEX2P) ----
-// Tiling of the fluid passes: one wave per (fluid, 64 x rows tile, chunk of kz planes).
+// Tiling of the fluid passes: one wave (or workgroup) per (fluid, 64 x rows tile, chunk of
+// kz planes).
 struct DustGrid {
     int kz, rows;
     bool block;  // tiles of a workgroup (donor cell, FP64), else of a wave

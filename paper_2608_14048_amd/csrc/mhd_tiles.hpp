@@ -769,7 +769,8 @@ struct FluxTile {
 // The FP64 PPM kernels reach three (168 registers) only in their reload form (see
 // FluxTile::kLean): the carried form held to three spilled about 36 dwords per lane and
 // ran 20 % slower (3.48 against 2.91 ms per corrector launch at 256^3), the reload form
-// ran 2.51 against 2.67 ms (with branch-free limiters 2.08, three dwords spilled).
+// ran 2.51 against 2.67 ms (with branch-free limiters 2.08; eight dwords spilled, most of
+// them by the second march for values that are not finite).
 template <int RECON, int RS, class R>
 struct FluxWaves {
     static constexpr int min = sizeof(R) == 4 ? 4 : (RS == 1 && RECON == 1 ? 2 : 3);
